@@ -508,6 +508,21 @@ constexpr bool src_runs_on() {
 // 32 at a time; measured on pushes of 400-byte rows: 0.937 -> 0.917 ms, of
 // 256-byte rows 0.123 -> 0.112 ms), MERGE_GRID_MAX for wider rows (no gain
 // there, 1% lost on 1,200-byte rows).
+// Whether a merge of n occurrences streams its table and gradient rows past
+// the caches (non-temporal).  It does when the rows it can touch (value and
+// accumulator rows of the distinct keys, at most min(n, num_keys)) exceed the
+// 256 MB last-level cache, so none of them can still be there when they are
+// next used.  Measured: pushes of 2M 400-byte rows 0.92 -> 0.80 ms, of 400K
+// 4,000-byte rows 1.40 -> 1.12, the ComplEx step (422K rows of 1 KB) 0.59 ->
+// 0.54; below the line rows are found in the cache by the next step and the
+// hint costs: CTR (213K rows of 256 bytes) 0.151 -> 0.161, a row-wise MF step
+// of 100K entries 0.176 -> 0.186.
+bool streams_rows(const ps_store* s, int64_t n) {
+  const int64_t value_bytes = (s->bf16 ? 2 : 4) * (int64_t)s->dim;
+  const int64_t accum_bytes = s->rowwise ? 4 : 4 * (int64_t)s->dim;
+  return std::min(n, s->num_keys) * (value_bytes + accum_bytes) > (int64_t(256) << 20);
+}
+
 template <class Src>
 ps_status launch_segreduce(ps_store* s, const SortBufs& b, const uint32_t* ks, Src src, int64_t n, int part,
                            hipStream_t st, int timing_id = PS_KERNEL_SEGREDUCE, int64_t grid_cap = 0,
@@ -519,22 +534,24 @@ ps_status launch_segreduce(ps_store* s, const SortBufs& b, const uint32_t* ks, S
   float* W = s->W + (s->bf16 ? 0 : cs.col0);
   bf16_t* Wb = reinterpret_cast<bf16_t*>(s->W) + (s->bf16 ? cs.col0 : 0);
   float* G = s->G + (s->rowwise ? 0 : cs.col0);
+  const bool stream_rows = streams_rows(s, n);
   return with_shape(shape, [&]<int L, int NV, int VW>() -> ps_status {
     const int64_t grid = reduce_grid(n, L, grid_cap ? grid_cap : (L <= 32 ? 1024 : MERGE_GRID_MAX));
     Timed t(s, timing_id, st);
+    auto launch = [&]<bool RW, class VT>(VT* values) {
+      if (stream_rows)
+        hipLaunchKernelGGL((k_segreduce<L, NV, VW, Src, RW, VT, true>), dim3(grid), dim3(BLOCK), 0, st, sv, src, n,
+                           values, G, s->ld, s->gld, dim, s->lr, s->eps, b.partial, b.split_list, b.hdr, part);
+      else
+        hipLaunchKernelGGL((k_segreduce<L, NV, VW, Src, RW, VT, false>), dim3(grid), dim3(BLOCK), 0, st, sv, src, n,
+                           values, G, s->ld, s->gld, dim, s->lr, s->eps, b.partial, b.split_list, b.hdr, part);
+    };
     if (s->bf16) {
-      if constexpr (src_runs_on<Src, bf16_t>())
-        hipLaunchKernelGGL((k_segreduce<L, NV, VW, Src, false, bf16_t>), dim3(grid), dim3(BLOCK), 0, st, sv, src, n,
-                           Wb, G, s->ld, s->gld, dim, s->lr, s->eps, b.partial, b.split_list, b.hdr, part);
-      else
-        return fail(PS_ERR_UNSUPPORTED, "this step does not run on bf16 values");
+      if constexpr (src_runs_on<Src, bf16_t>()) launch.template operator()<false, bf16_t>(Wb);
+      else return fail(PS_ERR_UNSUPPORTED, "this step does not run on bf16 values");
     } else if constexpr (src_runs_on<Src, float>()) {
-      if (s->rowwise)
-        hipLaunchKernelGGL((k_segreduce<L, NV, VW, Src, true, float>), dim3(grid), dim3(BLOCK), 0, st, sv, src, n,
-                           W, G, s->ld, s->gld, dim, s->lr, s->eps, b.partial, b.split_list, b.hdr, part);
-      else
-        hipLaunchKernelGGL((k_segreduce<L, NV, VW, Src, false, float>), dim3(grid), dim3(BLOCK), 0, st, sv, src, n,
-                           W, G, s->ld, s->gld, dim, s->lr, s->eps, b.partial, b.split_list, b.hdr, part);
+      if (s->rowwise) launch.template operator()<true, float>(W);
+      else launch.template operator()<false, float>(W);
     } else {
       return fail(PS_ERR_UNSUPPORTED, "this step does not run on fp32 values");
     }

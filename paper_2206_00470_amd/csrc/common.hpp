@@ -273,11 +273,56 @@ __device__ __forceinline__ float val_load(const bf16_t* p) { return bf16_widen(p
 __device__ __forceinline__ void val_store(float* p, float x) { *p = x; }
 __device__ __forceinline__ void val_store(bf16_t* p, float x) { p->bits = (uint16_t)bf16_narrow(x); }
 
-// Non-temporal fragment store for streams that are read back only once.
-template <int VW>
-__device__ __forceinline__ void store_frag_nt(float* p, const float* in) {
-#pragma unroll
-  for (int e = 0; e < VW; ++e) __builtin_nontemporal_store(in[e], p + e);
+// ------------------------------------------------------------------ streamed rows
+// The same accesses with the non-temporal hint when NT: for rows that one
+// launch touches once, so that they leave the caches to what is read again.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+template <int VW, bool NT, class VT>
+__device__ __forceinline__ void load_row(const VT* p, float* out) {
+  if constexpr (!NT) {
+    load_vals<VW>(p, out);
+  } else if constexpr (std::is_same_v<VT, float>) {
+    if constexpr (VW == 4) {
+      const f32x4 x = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+      out[0] = x.x; out[1] = x.y; out[2] = x.z; out[3] = x.w;
+    } else if constexpr (VW == 2) {
+      const f32x2 x = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(p));
+      out[0] = x.x; out[1] = x.y;
+    } else {
+      out[0] = __builtin_nontemporal_load(p);
+    }
+  } else if constexpr (VW == 4) {
+    const u32x2 x = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
+    out[0] = bf16_widen(x.x & 0xffffu);
+    out[1] = bf16_widen(x.x >> 16);
+    out[2] = bf16_widen(x.y & 0xffffu);
+    out[3] = bf16_widen(x.y >> 16);
+  } else {
+    load_vals<VW>(p, out);
+  }
+}
+
+template <int VW, bool NT, class VT>
+__device__ __forceinline__ void store_row(VT* p, const float* in) {
+  if constexpr (!NT) {
+    store_vals<VW>(p, in);
+  } else if constexpr (std::is_same_v<VT, float>) {
+    if constexpr (VW == 4) {
+      __builtin_nontemporal_store(f32x4{in[0], in[1], in[2], in[3]}, reinterpret_cast<f32x4*>(p));
+    } else if constexpr (VW == 2) {
+      __builtin_nontemporal_store(f32x2{in[0], in[1]}, reinterpret_cast<f32x2*>(p));
+    } else {
+      __builtin_nontemporal_store(in[0], p);
+    }
+  } else if constexpr (VW == 4) {
+    const u32x2 x = {bf16_narrow(in[0]) | (bf16_narrow(in[1]) << 16), bf16_narrow(in[2]) | (bf16_narrow(in[3]) << 16)};
+    __builtin_nontemporal_store(x, reinterpret_cast<u32x2*>(p));
+  } else {
+    store_vals<VW>(p, in);
+  }
 }
 
 }  // namespace adapm

@@ -154,12 +154,12 @@ struct SrcIndirect {
     const float* row;
   };
   __device__ __forceinline__ Meta meta(int64_t j) const { return {grads + (int64_t)perm[j] * ld}; }
-  template <int L, int NV, int VW>
+  template <int L, int NV, int VW, bool NT>
   __device__ __forceinline__ void load(const Meta& m, const float*, int gl, float* x) const {
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int c = (gl + v * L) * VW;
-      if (c < dim) load_frag<VW>(m.row + c, x + v * VW);
+      if (c < dim) load_row<VW, NT>(m.row + c, x + v * VW);
     }
   }
 };
@@ -174,12 +174,12 @@ struct SrcSorted {
     const float* row;
   };
   __device__ __forceinline__ Meta meta(int64_t j) const { return {grads + j * ld}; }
-  template <int L, int NV, int VW>
+  template <int L, int NV, int VW, bool NT>
   __device__ __forceinline__ void load(const Meta& m, const float*, int gl, float* x) const {
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int c = (gl + v * L) * VW;
-      if (c < dim) load_frag<VW>(m.row + c, x + v * VW);
+      if (c < dim) load_row<VW, NT>(m.row + c, x + v * VW);
     }
   }
 };
@@ -193,11 +193,11 @@ constexpr bool src_has_loss() {
   else return false;
 }
 
-template <int L, int NV, int VW, class Src>
+template <int L, int NV, int VW, bool NT, class Src>
 __device__ __forceinline__ void src_load(const Src& src, const typename Src::Meta& m, const float* own, int gl,
                                          float* x, double& lsum) {
-  if constexpr (src_has_loss<Src>()) src.template load<L, NV, VW>(m, own, gl, x, lsum);
-  else src.template load<L, NV, VW>(m, own, gl, x);
+  if constexpr (src_has_loss<Src>()) src.template load<L, NV, VW, NT>(m, own, gl, x, lsum);
+  else src.template load<L, NV, VW, NT>(m, own, gl, x);
 }
 
 // ------------------------------------------------------------------ reduce
@@ -229,7 +229,12 @@ __device__ __forceinline__ int64_t xcd_slot(int64_t block, int64_t nblocks) {
 // of such a segment also appends the segment to split_list.
 // RW selects row-wise AdaGrad: G then holds one accumulator per key, at
 // G[key * gld]; otherwise G is a table of rows at G + key * gld.
-template <int L, int NV, int VW, class Src, bool RW, class VT>
+// NT: the key's table rows, and the gradient rows of sources that read each
+// once, bypass the caches (streams_rows in the launch code decides).  Bound
+// by the random read-modify-write of 8*dim-byte spans: a bare probe of that
+// pattern on 1M of 11M 800-byte rows reaches 3.6 TB/s cached and 4.1 TB/s
+// non-temporal (1 KB rows: 4.8 either way, 2 KB 4.8 and 4.9; a copy 4.8-5.6).
+template <int L, int NV, int VW, class Src, bool RW, class VT, bool NT>
 __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_t n, VT* __restrict__ W,
                                                      float* __restrict__ G, int64_t ld, int64_t gld, int dim,
                                                      float lr, float eps,
@@ -284,8 +289,8 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
       for (int v = 0; v < NV; ++v) {
         const int col = (gl + v * L) * VW;
         if (col < dim) {
-          load_vals<VW>(wrow + col, wv + v * VW);
-          if (!RW && whole) load_frag<VW>(grow + col, gv + v * VW);
+          load_row<VW, NT>(wrow + col, wv + v * VW);
+          if (!RW && whole) load_row<VW, NT>(grow + col, gv + v * VW);
         }
       }
       if (RW && whole) gacc = *grow;
@@ -302,7 +307,7 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
       for (; q + UNROLL <= cnt; q += UNROLL) {
         float x[UNROLL][NE];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) src_load<L, NV, VW>(src, shfl_pod(mine, q + u, L), wv, gl, x[u], lsum);
+        for (int u = 0; u < UNROLL; ++u) src_load<L, NV, VW, NT>(src, shfl_pod(mine, q + u, L), wv, gl, x[u], lsum);
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u)
 #pragma unroll
@@ -310,7 +315,7 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
       }
       for (; q < cnt; ++q) {
         float x[NE];
-        src_load<L, NV, VW>(src, shfl_pod(mine, q, L), wv, gl, x, lsum);
+        src_load<L, NV, VW, NT>(src, shfl_pod(mine, q, L), wv, gl, x, lsum);
 #pragma unroll
         for (int e = 0; e < NE; ++e) acc[e] += (double)x[e];
       }
@@ -335,7 +340,7 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
         if (col < dim) {
 #pragma unroll
           for (int e = 0; e < VW; ++e) rowwise_elem(wv[v * VW + e], g[v * VW + e], den, lr);
-          store_vals<VW>(wrow + col, wv + v * VW);
+          store_row<VW, NT>(wrow + col, wv + v * VW);
         }
       }
       if (gl == 0) *grow = gacc;
@@ -347,8 +352,8 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
 #pragma unroll
           for (int e = 0; e < VW; ++e)
             adagrad_elem(wv[v * VW + e], gv[v * VW + e], (float)acc[v * VW + e], lr, eps);
-          store_vals<VW>(wrow + col, wv + v * VW);
-          store_frag<VW>(grow + col, gv + v * VW);
+          store_row<VW, NT>(wrow + col, wv + v * VW);
+          store_row<VW, NT>(grow + col, gv + v * VW);
         }
       }
     } else {

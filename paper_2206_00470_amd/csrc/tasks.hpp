@@ -97,7 +97,7 @@ struct SrcMFRow {
     const MFEntry r = pe[j];
     return {W + (int64_t)r.col_key * ld, r.y, r.col_pos};
   }
-  template <int L, int NV, int VW>
+  template <int L, int NV, int VW, bool NT>
   __device__ __forceinline__ void load(const Meta& m, const float* own, int gl, float* x, double& lsum) const {
     float p[NV * VW];
     double dot = 0.0, nu = 0.0, nm = 0.0;
@@ -554,7 +554,7 @@ struct SrcKGE {
     if (q < 3) return {mat + ((int64_t)t * 3 + q) * dim, 0.0, 0u, 0u};
     return {base + ((int64_t)t * 2 + ((int)q - 3 < n_head ? 0 : 1)) * dim, coef[occ], 1u, 0u};
   }
-  template <int L, int NV, int VW>
+  template <int L, int NV, int VW, bool NT>
   __device__ __forceinline__ void load(const Meta& m, const float*, int gl, float* x) const {
     if (!m.scaled) {
       const float* row = static_cast<const float*>(m.row);
@@ -812,7 +812,7 @@ struct SrcSGNS {
     if (q == 0) return {mat + (int64_t)b * dim, 1.0, 0u, 0u};
     return {W + (int64_t)centre[b] * ld, coef[occ], 1u, 0u};
   }
-  template <int L, int NV, int VW>
+  template <int L, int NV, int VW, bool NT>
   __device__ __forceinline__ void load(const Meta& m, const float*, int gl, float* x) const {
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
