@@ -4,6 +4,7 @@
 
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -818,14 +819,54 @@ struct PlanWD {
   double* slices = nullptr;  // split-K partial products of the weight gradients
 };
 
-// K slices of a weight-gradient product (K = the batch): enough workgroups
-// to fill the chip (about 1024), slices of at least 256 rows.
-int64_t wgrad_slices(int64_t M, int64_t N, int64_t K) {
-  const int64_t blocks = ceil_div(M, GEMM_BM) * ceil_div(N, GEMM_BN);
-  int64_t S = ceil_div(1024, blocks);
-  S = std::min<int64_t>(S, std::max<int64_t>(1, K / 256));
-  return std::max<int64_t>(1, std::min<int64_t>(S, 32));
+// Tile and K slices of a product.  All tiles of a product take equally long,
+// so its time is the number of rounds the busiest compute unit works (tiles
+// over 256 units, rounded up) times a tile's K steps, plus, when K is split,
+// the partial products' way through memory.  Smaller tiles are chosen where
+// they fill the last round better (8,192 x 1,664 over K = 1,024 is 832 tiles
+// of 128 x 128, 3.25 rounds and 4 worked, but 1,664 of 64 x 128, 6.5 and 7) or
+// where a small product leaves units idle; a step of the smallest takes about
+// as long as its operands are under way, so there is none below.  Split K
+// (the weight gradients, whose K is the batch) takes the S with the smallest
+// sum, slices of at least 256 rows: 1,664 x 1,024 over K = 8,192 with S = 10
+// left a fifth of its fifth round idle.
+struct GemmPlan {
+  int tm, tn;
+  int64_t slices;
+};
+
+GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool split) {
+  constexpr double kUnits = 256;
+  constexpr double kStep = 4096 / 2400.0;          // us per 16 K steps of a 128 x 128 tile
+  constexpr double kBytesPerUs = 4e6;              // slices written, then read and added
+  constexpr double kLone = 1.1;                    // one workgroup alone on a unit hides less latency
+  // the smallest tile loads twice as much per product: with no price on that,
+  // a step of 8,192 samples x 26 fields of 64 through 3 x 1,024 takes 3.47 ms
+  // instead of 3.26; steps of 1,571 x 15 x 36 through 2 x 221 take 0.23 ms
+  // with it and 0.29 without (0.81 with 128 x 128 tiles staged through LDS)
+  constexpr int kTiles[3][2] = {{128, 128}, {64, 128}, {64, 64}};
+  constexpr double kTileCost[3] = {1.0, 1.0, 1.25};
+  GemmPlan best{128, 128, 1};
+  double best_us = -1.0;
+  const int64_t smax = split ? std::max<int64_t>(1, std::min<int64_t>(32, K / 256)) : 1;
+  for (int q = 0; q < 3; ++q)
+    for (int64_t S = 1; S <= smax; ++S) {
+      const int* tile = kTiles[q];
+      const double tiles = (double)(ceil_div(M, tile[0]) * ceil_div(N, tile[1]) * S);
+      const double rounds = std::ceil(tiles / kUnits);
+      const double steps = (double)ceil_div(ceil_div(K, S), GEMM_BK);
+      double us = rounds * steps * kStep * (tile[0] * tile[1]) / (128.0 * 128.0) * kTileCost[q];
+      if (rounds < 2.0) us *= kLone;
+      if (S > 1) us += 2.0 * (double)S * (double)M * (double)N * 8.0 / kBytesPerUs;
+      if (best_us < 0.0 || us < 0.98 * best_us) {
+        best_us = us;
+        best = GemmPlan{tile[0], tile[1], S};
+      }
+    }
+  return best;
 }
+
+int64_t wgrad_slices(int64_t M, int64_t N, int64_t K) { return gemm_plan(M, N, K, true).slices; }
 
 void plan_wd(void* ws, int dim, int64_t B, int F, int E, int L, const int32_t* hidden, PlanWD* p) {
   const int64_t n = B * F;
@@ -853,20 +894,28 @@ void plan_wd(void* ws, int dim, int64_t B, int F, int E, int L, const int32_t* h
   p->base.bytes = c.off + 256;
 }
 
-// One product; with S > 1 K is split into S slices whose partial products go
-// to `slices` (S * M * N doubles) and are then added in order into C (which
-// must then be dense: ldc = N, plain store).
-template <bool TA, bool TB, typename BT>
+// One product; with `slices` K is split as gemm_plan says, the partial
+// products go to `slices` (S * M * N doubles) and are then added in order into
+// C (which must then be dense: ldc = N, no epilogue).
+template <bool TA, bool TB, typename BT, int EPI = EPI_NONE>
 ps_status gemm(ps_store* s, int64_t M, int64_t N, int64_t K, const double* A, int64_t lda, const BT* B, int64_t ldb,
-               double* C, int64_t ldc, hipStream_t st, int64_t S = 1, double* slices = nullptr) {
-  const int64_t gy = ceil_div(M, GEMM_BM), gx = ceil_div(N, GEMM_BN);
-  if (gy > 65535) return fail(PS_ERR_UNSUPPORTED, "%lld rows exceed the product kernel's grid", (long long)M);
-  const int64_t kslice = S > 1 ? ceil_div(ceil_div(K, S), GEMM_BK) * GEMM_BK : K;
-  S = S > 1 ? ceil_div(K, kslice) : 1;
+               double* C, int64_t ldc, hipStream_t st, double* slices = nullptr, const float* bias = nullptr,
+               const double* H = nullptr) {
+  const GemmPlan g = gemm_plan(M, N, K, slices != nullptr);
+  const int64_t gy = ceil_div(M, g.tm), gx = ceil_div(N, g.tn);
+  if (ceil_div(M, 128) > 65535) return fail(PS_ERR_UNSUPPORTED, "%lld rows exceed the product kernel's grid", (long long)M);
+  const int64_t kslice = g.slices > 1 ? ceil_div(ceil_div(K, g.slices), GEMM_BK) * GEMM_BK : K;
+  const int64_t S = g.slices > 1 ? ceil_div(K, kslice) : 1;
+  if (gx * gy * S > INT32_MAX) return fail(PS_ERR_UNSUPPORTED, "%lld x %lld exceed the product kernel's grid", (long long)M, (long long)N);
   {
     Timed t(s, PS_KERNEL_MLP, st);
-    hipLaunchKernelGGL((k_gemm_f64<TA, TB, BT>), dim3(gx, gy, S), dim3(BLOCK), 0, st, M, N, K, A, lda, B, ldb,
-                       S > 1 ? slices : C, S > 1 ? N : ldc, kslice);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(gx * gy * S), dim3(BLOCK), 0, st, M, N, K, A, lda, B, ldb, S > 1 ? slices : C,
+                         S > 1 ? N : ldc, kslice, (int)gx, (int)gy, bias, H);
+    };
+    if (g.tm == 128) launch(k_gemm_f64<TA, TB, BT, 128, 128, EPI>);
+    else if (g.tn == 128) launch(k_gemm_f64<TA, TB, BT, 64, 128, EPI>);
+    else launch(k_gemm_f64<TA, TB, BT, 64, 64, EPI>);
     LAUNCHED(k_gemm_f64);
     if (S > 1) {
       hipLaunchKernelGGL(k_sum_slices, dim3(small_grid(M * N, BLOCK, 4096)), dim3(BLOCK), 0, st, slices, S, M * N, C);
@@ -879,9 +928,10 @@ ps_status gemm(ps_store* s, int64_t M, int64_t N, int64_t K, const double* A, in
 ps_status colsum(const double* A, int64_t rows, int64_t cols, const double* scale, double* part, double* out,
                  hipStream_t st) {
   const int64_t ny = ceil_div(rows, COLSUM_ROWS);
-  hipLaunchKernelGGL(k_colsum_part, dim3(ceil_div(cols, BLOCK), ny), dim3(BLOCK), 0, st, A, rows, cols, scale, part);
+  hipLaunchKernelGGL(k_colsum_part, dim3(ceil_div(cols, COLSUM_COLS), ny), dim3(BLOCK), 0, st, A, rows, cols, scale,
+                     part);
   LAUNCHED(k_colsum_part);
-  hipLaunchKernelGGL(k_colsum_final, dim3(ceil_div(cols, BLOCK)), dim3(BLOCK), 0, st, part, ny, cols, out);
+  hipLaunchKernelGGL(k_colsum_final, dim3(ceil_div(cols, COLSUM_COLS)), dim3(BLOCK), 0, st, part, ny, cols, out);
   LAUNCHED(k_colsum_final);
   return PS_OK;
 }
@@ -1964,12 +2014,10 @@ ps_status ps_step_ctr_wd(ps_store* s, const int64_t* keys, const float* label, i
   const double* h = p.X;
   int64_t fan = K0;
   for (int l = 0; l < L; ++l) {
-    if (ps_status r = gemm<false, false, float>(s, B, hidden[l], fan, h, fan, dense + d.offW[l], hidden[l], p.H[l],
-                                                hidden[l], st))
+    if (ps_status r = gemm<false, false, float, EPI_BIAS_RELU>(s, B, hidden[l], fan, h, fan, dense + d.offW[l],
+                                                               hidden[l], p.H[l], hidden[l], st, nullptr,
+                                                               dense + d.offb[l]))
       return r;
-    hipLaunchKernelGGL(k_bias_relu, dim3(small_grid(B * hidden[l], BLOCK, 8192)), dim3(BLOCK), 0, st, p.H[l], B,
-                       (int64_t)hidden[l], dense + d.offb[l]);
-    LAUNCHED(k_bias_relu);
     h = p.H[l];
     fan = hidden[l];
   }
@@ -1991,16 +2039,15 @@ ps_status ps_step_ctr_wd(ps_store* s, const int64_t* keys, const float* label, i
     const int64_t fin = l > 0 ? hidden[l - 1] : K0;
     const int64_t fout = hidden[l];
     if (ps_status r = gemm<true, false, double>(s, fin, fout, B, hp, fin, cur, fout, p.dg + d.offW[l], fout, st,
-                                                wgrad_slices(fin, fout, B), p.slices))
+                                                p.slices))
       return r;
     if (ps_status r = colsum(cur, B, fout, nullptr, p.part, p.dg + d.offb[l], st)) return r;
     double* next = cur == p.dA ? p.dB : p.dA;
-    if (ps_status r = gemm<false, true, float>(s, B, fin, fout, cur, fout, dense + d.offW[l], fout, next, fin, st))
-      return r;
-    if (l > 0) {
-      hipLaunchKernelGGL(k_relu_mask, dim3(small_grid(B * fin, BLOCK, 8192)), dim3(BLOCK), 0, st, next, hp, B * fin);
-      LAUNCHED(k_relu_mask);
-    }
+    // the gradient of the layer below, masked by its ReLU (the inputs have none)
+    ps_status r = l > 0 ? gemm<false, true, float, EPI_RELU_MASK>(s, B, fin, fout, cur, fout, dense + d.offW[l], fout,
+                                                                  next, fin, st, nullptr, nullptr, hp)
+                        : gemm<false, true, float>(s, B, fin, fout, cur, fout, dense + d.offW[l], fout, next, fin, st);
+    if (r) return r;
     cur = next;
   }
   // per-occurrence embedding gradient rows, at their sorted positions

@@ -9,6 +9,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "push.hpp"
 
 namespace adapm {
 
@@ -17,149 +18,209 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // ------------------------------------------------------------------ GEMM
 // C[M][N] = op(A)[M][K] op(B)[K][N], all sums in fp64.
 // op(A)[m][k] = TA ? A[k * lda + m] : A[m * lda + k]; op(B) likewise with
-// TB.  B's elements are fp32 (the dense parameters) or fp64.  The bias and
-// ReLU of a forward layer and the ReLU mask of a backward one are applied
-// by k_bias_relu / k_relu_mask afterwards: an epilogue with arithmetic would
-// copy the 128 accumulator registers into ordinary ones and halve the
-// workgroups a compute unit holds.
+// TB.  B's elements are fp32 (the dense parameters) or fp64.
 //
-// A workgroup computes a 128 x 128 tile of C, each of its four wavefronts a
-// 64 x 64 quarter as 4 x 4 products of 16 x 16.  K advances 16 at a time
-// through two LDS buffers, one barrier per step; the operands of the step
-// after next are loaded into registers while the matrix cores work on the
-// current buffer (two register sets, so each load has two steps to land),
-// and the next step's registers are stored to the other buffer.  With gridDim.z = S > 1 the K range
-// is split into S slices and slice z writes its partial product to
-// C + z * M * N (plain store only); k_sum_slices adds them in slice order.
-constexpr int GEMM_BM = 128, GEMM_BN = 128, GEMM_BK = 16;
-constexpr int GEMM_PAD = 0;   // doubles of padding per LDS row (padding measured no faster)
+// A workgroup computes a TM x TN tile of C (128 x 128, 64 x 128 or 64 x 64),
+// each of its four wavefronts a quarter as products of 16 x 16, with no LDS
+// and no barrier: a fp64 16x16x4 product occupies its matrix core for 64
+// cycles, so a wave's 64 products of 16 K steps (128 x 128) take 4,096 cycles
+// and need 12-16 KB of operands, which the L1 and L2 deliver in a fifth of
+// that time; each wave loads the next K step's operands into a second
+// register set while the matrix cores work on the current one, and waits for
+// nobody.  Which k a lane group multiplies is free as long as both operands
+// agree, and so are the rows and columns of a product: lane group g takes the
+// KK neighbouring k at KK g of a step, and lane position r the MI
+// neighbouring rows (NJ columns) at MI r (NJ r), so that every load is a
+// vector of neighbouring elements and a lane stores neighbouring results.
+// Counters at 8,192 x 1,024 over K = 1,024: matrix cores busy 77-84% of the
+// time, 61-66 TFLOP/s.  Staging the operands through LDS with a barrier per
+// 16 K steps reached 52-57, and 39 where the fp32 operand was converted next
+// to its load, which then was waited for at once.
+//
+// Rows and columns past the end are clamped to the last ones that exist: the
+// lanes compute and store those results twice, with equal bits, and no access
+// needs a predicate.  Only the last K step, and products with fewer rows or
+// columns than one lane's vector, load element by element.
+//
+// Tiles are dealt to the dies in contiguous runs (xcd_slot), so the tiles
+// that share A's rows, and the slices of a split K, stay in one L2.  With S > 1
+// slices of K, slice z writes its partial product to C + z * M * N (EPI_NONE
+// only); k_sum_slices adds them in slice order.
+//
+// EPI_BIAS_RELU: C = max(product + bias[n], 0), a forward layer.
+// EPI_RELU_MASK: C = H[m][n] > 0 ? product : 0, the gradient of the layer
+// below (H its activations, same shape and stride as C).
+constexpr int GEMM_BK = 16;   // K slices are multiples of this
+enum { EPI_NONE = 0, EPI_BIAS_RELU = 1, EPI_RELU_MASK = 2 };
 
-template <bool TA, bool TB, typename BT>
+// n neighbouring elements (8, 16 or 32 bytes), aligned like one element.
+template <typename T, int n>
+__device__ __forceinline__ void load_elems(const T* __restrict__ p, T* out) {
+  if constexpr (n == 4 && sizeof(T) == 8) {
+    load_elems<T, 2>(p, out);
+    load_elems<T, 2>(p + 2, out + 2);
+  } else {
+    typedef T vec __attribute__((ext_vector_type(n), aligned(sizeof(T))));
+    const vec x = *reinterpret_cast<const vec*>(p);
+#pragma unroll
+    for (int e = 0; e < n; ++e) out[e] = x[e];
+  }
+}
+
+// One wave's operand of a K step: v[kk][i] is element i of the lane's ROWS
+// neighbouring rows (columns of B) at k = KK g + kk.  KMAJOR: memory rows run
+// along k (the lane's rows are neighbours in memory), else along the rows.
+template <typename T, int KK, int ROWS, bool KMAJOR>
+struct GemmOperand {
+  T v[KK][ROWS];
+  __device__ __forceinline__ void load(const T* __restrict__ p, int64_t ld) {   // p: the lane's first element
+    if constexpr (KMAJOR) {
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) load_elems<T, ROWS>(p + kk * ld, v[kk]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i) {
+        T x[KK];
+        load_elems<T, KK>(p + i * ld, x);
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) v[kk][i] = x[kk];
+      }
+    }
+  }
+  // element by element: rows clamped to nr - 1, zeros from k = kend on
+  __device__ __forceinline__ void load_edge(const T* __restrict__ base, int64_t ld, int64_t row, int64_t nr, int64_t k,
+                                            int64_t kend) {
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i) {
+        const int64_t r = row + i < nr ? row + i : nr - 1;
+        const int64_t q = k + kk;
+        v[kk][i] = q < kend ? base[KMAJOR ? q * ld + r : r * ld + q] : T(0);
+      }
+  }
+};
+
+template <bool TA, bool TB, typename BT, int TM, int TN, int EPI>
 __global__ __launch_bounds__(BLOCK, 2) void k_gemm_f64(int64_t M, int64_t N, int64_t K, const double* __restrict__ A,
-                                                    int64_t lda, const BT* __restrict__ B, int64_t ldb,
-                                                    double* __restrict__ C, int64_t ldc, int64_t kslice) {
-  __shared__ double As[2][GEMM_BK][GEMM_BM + GEMM_PAD];   // [buffer][k][m]
-  __shared__ double Bs[2][GEMM_BK][GEMM_BN + GEMM_PAD];   // [buffer][k][n]
-  const int t = threadIdx.x;
-  const int lane = t % WAVE;
-  const int wave = t / WAVE;
-  const int64_t m0 = (int64_t)blockIdx.y * GEMM_BM;
-  const int64_t n0 = (int64_t)blockIdx.x * GEMM_BN;
-  const int64_t kbeg = (int64_t)blockIdx.z * kslice;
+                                                       int64_t lda, const BT* __restrict__ B, int64_t ldb,
+                                                       double* __restrict__ C, int64_t ldc, int64_t kslice, int gx,
+                                                       int gy, const float* __restrict__ bias,
+                                                       const double* __restrict__ H) {
+  constexpr int MI = TM / 32, NJ = TN / 32;   // products of a wave along m and n
+  constexpr int KK = sizeof(BT) == 4 ? 4 : 2; // k per lane group and step (two register sets have to fit)
+  constexpr int STEP = 4 * KK;
+  const int lane = threadIdx.x % WAVE;
+  const int wave = threadIdx.x / WAVE;
+  const int r = lane % 16, g = lane / 16;
+  const int id = (int)xcd_slot(blockIdx.x, gridDim.x);
+  const int64_t m0 = (int64_t)(id / gx % gy) * TM + (wave / 2) * (TM / 2);
+  const int64_t n0 = (int64_t)(id % gx) * TN + (wave % 2) * (TN / 2);
+  const int64_t z = id / (gx * gy);
+  const int64_t kbeg = z * kslice;
   const int64_t kend = kbeg + kslice < K ? kbeg + kslice : K;
-  if (gridDim.z > 1) C += (int64_t)blockIdx.z * M * N;
-  const int wm = (wave / 2) * 64;   // the wave's 64 x 64 quarter of the tile
-  const int wn = (wave % 2) * 64;
+  C += z * M * N;
+  // first row (column) of lane position q, so that the vector stays inside
+  const bool vec = M >= MI && N >= NJ;
+  auto row_of = [&](int q) -> int64_t {
+    const int64_t m = m0 + MI * q;
+    return !vec || m < M - MI ? m : M - MI;
+  };
+  auto col_of = [&](int q) -> int64_t {
+    const int64_t n = n0 + NJ * q;
+    return !vec || n < N - NJ ? n : N - NJ;
+  };
+  const int64_t row = row_of(r), col = col_of(r);
+  const double* pa = A + (TA ? (kbeg + KK * g) * lda + row : row * lda + kbeg + KK * g);
+  const BT* pb = B + (TB ? col * ldb + kbeg + KK * g : (kbeg + KK * g) * ldb + col);
+  const int64_t da = TA ? STEP * lda : STEP, db = TB ? STEP : STEP * ldb;
 
-  // the thread's 8 elements of each operand tile: A (TA = false) rows t/2,
-  // k (t%2)*8..+8; A (TA) k t/16, m (t%16)*8..+8; B likewise
-  const int ar = TA ? t / 16 : t / 2;            // TA: k row; else m row
-  const int aq = TA ? (t % 16) * 8 : (t % 2) * 8;
-  const int br = TB ? t / 2 : t / 16;            // TB: n row; else k row
-  const int bq = TB ? (t % 2) * 8 : (t % 16) * 8;
-  double ra_[2][8], rb_[2][8];
-  auto load = [&]<int R>(int64_t k0) {
-    double* ra = ra_[R];
-    double* rb = rb_[R];
+  struct Set {
+    GemmOperand<double, KK, MI, TA> a;
+    GemmOperand<BT, KK, NJ, !TB> b;
+  } set[2];
+  auto load = [&](Set& x) {
+    x.a.load(pa, lda);
+    x.b.load(pb, ldb);
+    pa += da;
+    pb += db;
+  };
+
+  f64x4 acc[MI][NJ];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      if constexpr (!TA) {
-        const int64_t m = m0 + ar, k = k0 + aq + e;
-        ra[e] = (m < M && k < kend) ? A[m * lda + k] : 0.0;
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  auto products = [&](const Set& x) {
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      double b[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) b[j] = (double)x.b.v[kk][j];
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.a.v[kk][i], b[j], acc[i][j], 0, 0, 0);
+    }
+  };
+  // whole steps in vectors, two at a time through the two sets, then the rest
+  const int64_t nfull = vec && kbeg < kend ? (kend - kbeg) / STEP : 0;
+  if (nfull > 0) load(set[0]);
+  for (int64_t s = 0; s < nfull; s += 2) {
+    if (s + 1 < nfull) load(set[1]);
+    products(set[0]);
+    if (s + 2 < nfull) load(set[0]);
+    if (s + 1 < nfull) products(set[1]);
+  }
+  for (int64_t k0 = kbeg + nfull * STEP; k0 < kend; k0 += STEP) {
+    set[0].a.load_edge(A, lda, row, M, k0 + KK * g, kend);
+    set[0].b.load_edge(B, ldb, col, N, k0 + KK * g, kend);
+    products(set[0]);
+  }
+  // result v of product (i, j): lane position g + 4 v along m, r along n
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      int64_t m = row_of(g + 4 * v) + i;
+      m = m < M ? m : M - 1;
+      double* out = C + m * ldc + col;
+      const double* h = EPI == EPI_RELU_MASK ? H + m * ldc + col : nullptr;
+      double x[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) x[j] = acc[i][j][v];
+      if (vec) {
+        if constexpr (EPI == EPI_BIAS_RELU) {
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            x[j] += (double)bias[col + j];
+            x[j] = x[j] > 0.0 ? x[j] : 0.0;
+          }
+        } else if constexpr (EPI == EPI_RELU_MASK) {
+          double hv[NJ];
+          load_elems<double, NJ>(h, hv);
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            if (!(hv[j] > 0.0)) x[j] = 0.0;
+        }
+        typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
+#pragma unroll
+        for (int j = 0; j < NJ; j += 2) *reinterpret_cast<f64x2u*>(out + j) = f64x2u{x[j], x[j + 1]};
       } else {
-        const int64_t k = k0 + ar, m = m0 + aq + e;
-        ra[e] = (m < M && k < kend) ? A[k * lda + m] : 0.0;
-      }
-      if constexpr (!TB) {
-        const int64_t k = k0 + br, n = n0 + bq + e;
-        rb[e] = (n < N && k < kend) ? (double)B[k * ldb + n] : 0.0;
-      } else {
-        const int64_t n = n0 + br, k = k0 + bq + e;
-        rb[e] = (n < N && k < kend) ? (double)B[n * ldb + k] : 0.0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          if (col + j >= N) continue;
+          if constexpr (EPI == EPI_BIAS_RELU) {
+            x[j] += (double)bias[col + j];
+            x[j] = x[j] > 0.0 ? x[j] : 0.0;
+          } else if constexpr (EPI == EPI_RELU_MASK) {
+            if (!(h[j] > 0.0)) x[j] = 0.0;
+          }
+          out[j] = x[j];
+        }
       }
     }
-  };
-  auto stash = [&]<int R>(int buf) {
-    const double* ra = ra_[R];
-    const double* rb = rb_[R];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      if constexpr (!TA) As[buf][aq + e][ar] = ra[e];
-      else As[buf][ar][aq + e] = ra[e];
-      if constexpr (!TB) Bs[buf][br][bq + e] = rb[e];
-      else Bs[buf][bq + e][br] = rb[e];
-    }
-  };
-
-  f64x4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
-
-  auto products = [&](int buf) {
-#pragma unroll
-    for (int ks = 0; ks < GEMM_BK; ks += 4) {
-      const int kr = ks + lane / 16;
-      double a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[buf][kr][wm + i * 16 + lane % 16];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[buf][kr][wn + j * 16 + lane % 16];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-  };
-  // step s: LDS buffer s % 2 holds its operands, register set (s + 1) % 2
-  // those of step s + 1; set s % 2 is free (stored at the end of step s - 1)
-  // and receives step s + 2.  The other buffer was last read in step s - 1,
-  // which every wave finished before that step's barrier.
-  const int64_t nsteps = kbeg < kend ? (kend - kbeg + GEMM_BK - 1) / GEMM_BK : 0;
-  auto step = [&]<int P>(int64_t s) {
-    if (s + 2 < nsteps) load.template operator()<P>(kbeg + (s + 2) * GEMM_BK);
-    products(P);
-    if (s + 1 < nsteps) stash.template operator()<1 - P>(1 - P);
-    __syncthreads();
-  };
-  if (nsteps > 0) {
-    load.template operator()<0>(kbeg);
-    stash.template operator()<0>(0);
-    if (nsteps > 1) load.template operator()<1>(kbeg + GEMM_BK);
-  }
-  __syncthreads();
-  for (int64_t s = 0; s < nsteps; s += 2) {
-    step.template operator()<0>(s);
-    if (s + 1 < nsteps) step.template operator()<1>(s + 1);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t m = m0 + wm + i * 16 + lane / 16 + 4 * v;
-        const int64_t n = n0 + wn + j * 16 + lane % 16;
-        if (m < M && n < N) C[m * ldc + n] = acc[i][j][v];
-      }
-}
-
-// H[m][n] = max(H[m][n] + bias[n], 0): a forward layer's bias and ReLU.
-__global__ __launch_bounds__(BLOCK) void k_bias_relu(double* __restrict__ H, int64_t M, int64_t N,
-                                                     const float* __restrict__ bias) {
-  const int64_t n_all = M * N;
-  for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < n_all; i += (int64_t)gridDim.x * BLOCK) {
-    const double x = H[i] + (double)bias[i % N];
-    H[i] = x > 0.0 ? x : 0.0;
-  }
-}
-
-// D[m][n] = 0 where H[m][n] <= 0: the ReLU derivative of the layer below.
-__global__ __launch_bounds__(BLOCK) void k_relu_mask(double* __restrict__ D, const double* __restrict__ H,
-                                                     int64_t count) {
-  for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < count; i += (int64_t)gridDim.x * BLOCK)
-    if (!(H[i] > 0.0)) D[i] = 0.0;
 }
 
 // out[i] = sum over z of part[z * count + i], z = 0 .. S-1 in order.
@@ -167,7 +228,15 @@ __global__ __launch_bounds__(BLOCK) void k_sum_slices(const double* __restrict__
                                                       double* __restrict__ out) {
   for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < count; i += (int64_t)gridDim.x * BLOCK) {
     double t = 0.0;
-    for (int64_t z = 0; z < S; ++z) t += part[z * count + i];
+    int64_t z = 0;
+    for (; z + 4 <= S; z += 4) {
+      double x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[q] = part[(z + q) * count + i];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) t += x[q];
+    }
+    for (; z < S; ++z) t += part[z * count + i];
     out[i] = t;
   }
 }
@@ -217,13 +286,25 @@ __global__ __launch_bounds__(BLOCK) void k_wd_head(const double* __restrict__ H,
   for (int64_t b = (int64_t)blockIdx.x * WAVES_PER_BLOCK + threadIdx.x / WAVE; b < B;
        b += (int64_t)gridDim.x * WAVES_PER_BLOCK) {
     const double* h = H + b * Hn;
-    double s = 0.0;
-    for (int64_t n = lane; n < Hn; n += WAVE) s += h[n] * (double)w[n];
-    s = group_sum<WAVE>(s);
-    double wide = 0.0;
     const bool valid = ok[b];
-    if (valid)
-      for (int f = 0; f < F; ++f) wide += (double)W[keys[b * F + f] * ld + E];
+    // the wide weights, one field per lane, added in field order
+    double wide = 0.0;
+    for (int f0 = 0; f0 < F; f0 += WAVE) {
+      const int nf = F - f0 < WAVE ? F - f0 : WAVE;
+      const float x = valid && lane < nf ? W[keys[b * F + f0 + lane] * ld + E] : 0.0f;
+      for (int f = 0; f < nf; ++f) wide += (double)__shfl(x, f, WAVE);
+    }
+    double s = 0.0;
+    int64_t n0 = lane;
+    for (; n0 + 7 * WAVE < Hn; n0 += 8 * WAVE) {   // eight loads in flight
+      double x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = h[n0 + q * WAVE];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s += x[q] * (double)w[n0 + q * WAVE];
+    }
+    for (; n0 < Hn; n0 += WAVE) s += h[n0] * (double)w[n0];
+    s = group_sum<WAVE>(s);
     const double logit = s + (double)c[0] + wide;
     const double y = (double)label[b];
     double g = 0.0;
@@ -234,7 +315,18 @@ __global__ __launch_bounds__(BLOCK) void k_wd_head(const double* __restrict__ H,
       g = (logit >= 0.0 ? 1.0 / (1.0 + exp(-logit)) : exp(logit) / (1.0 + exp(logit))) - y;
     }
     if (lane == 0) dlogit[b] = g;
-    for (int64_t n = lane; n < Hn; n += WAVE) dH[b * Hn + n] = (!relu || h[n] > 0.0) ? g * (double)w[n] : 0.0;
+    n0 = lane;
+    for (; n0 + 7 * WAVE < Hn; n0 += 8 * WAVE) {
+      double x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = h[n0 + q * WAVE];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int64_t n = n0 + q * WAVE;
+        dH[b * Hn + n] = (!relu || x[q] > 0.0) ? g * (double)w[n] : 0.0;
+      }
+    }
+    for (; n0 < Hn; n0 += WAVE) dH[b * Hn + n0] = (!relu || h[n0] > 0.0) ? g * (double)w[n0] : 0.0;
   }
   __shared__ double sm[WAVES_PER_BLOCK];
   lsum = block_sum_double(lsum, sm);
@@ -242,28 +334,54 @@ __global__ __launch_bounds__(BLOCK) void k_wd_head(const double* __restrict__ H,
 }
 
 // Column sums out[n] = sum_b A[b][n] s[b] (s = 1 without a scale), in two
-// deterministic stages: block (x, y) sums rows [y R, (y+1) R) of columns
-// x*BLOCK .. into part[y][n]; then the parts are added in y order.
-constexpr int64_t COLSUM_ROWS = 256;
+// deterministic stages: block (x, y) sums rows [y R, (y + 1) R) of 64 columns
+// into part[y][n], each of its four wavefronts every fourth row with eight
+// loads in flight, the wavefronts' sums added in order; then the parts are
+// added likewise.  Bound by reading A once: 128 rows per block give a batch of
+// 8,192 x 1,024 its 1,024 workgroups (256 rows of 256 columns, one load in
+// flight per thread, took 77 us for its 67 MB; a single column, 8 KB, as long).
+constexpr int64_t COLSUM_ROWS = 128;
+constexpr int COLSUM_COLS = 64;
+
+__device__ __forceinline__ void colsum_block(const double* __restrict__ A, int64_t r0, int64_t r1, int64_t cols,
+                                             const double* __restrict__ s, double* __restrict__ out) {
+  __shared__ double sm[WAVES_PER_BLOCK][COLSUM_COLS];
+  const int64_t n = (int64_t)blockIdx.x * COLSUM_COLS + threadIdx.x % WAVE;
+  const int w = threadIdx.x / WAVE;
+  const bool in = n < cols;
+  double t = 0.0;
+  int64_t r = r0 + w;
+  for (; r + 7 * WAVES_PER_BLOCK < r1; r += 8 * WAVES_PER_BLOCK) {
+    double x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = in ? A[(r + q * WAVES_PER_BLOCK) * cols + n] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) t += s ? x[q] * s[r + q * WAVES_PER_BLOCK] : x[q];
+  }
+  for (; r < r1; r += WAVES_PER_BLOCK) {
+    const double x = in ? A[r * cols + n] : 0.0;
+    t += s ? x * s[r] : x;
+  }
+  sm[w][threadIdx.x % WAVE] = t;
+  __syncthreads();
+  if (w == 0 && in) {
+    double a = sm[0][threadIdx.x];
+#pragma unroll
+    for (int q = 1; q < WAVES_PER_BLOCK; ++q) a += sm[q][threadIdx.x];
+    out[n] = a;
+  }
+}
 
 __global__ __launch_bounds__(BLOCK) void k_colsum_part(const double* __restrict__ A, int64_t rows, int64_t cols,
                                                        const double* __restrict__ s, double* __restrict__ part) {
-  const int64_t n = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  if (n >= cols) return;
   const int64_t r0 = (int64_t)blockIdx.y * COLSUM_ROWS;
   const int64_t r1 = r0 + COLSUM_ROWS < rows ? r0 + COLSUM_ROWS : rows;
-  double t = 0.0;
-  for (int64_t r = r0; r < r1; ++r) t += s ? A[r * cols + n] * s[r] : A[r * cols + n];
-  part[(int64_t)blockIdx.y * cols + n] = t;
+  colsum_block(A, r0, r1, cols, s, part + (int64_t)blockIdx.y * cols);
 }
 
 __global__ __launch_bounds__(BLOCK) void k_colsum_final(const double* __restrict__ part, int64_t nparts, int64_t cols,
                                                         double* __restrict__ out) {
-  const int64_t n = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  if (n >= cols) return;
-  double t = 0.0;
-  for (int64_t y = 0; y < nparts; ++y) t += part[y * cols + n];
-  out[n] = t;
+  colsum_block(part, 0, nparts, cols, nullptr, out);
 }
 
 // Per-occurrence gradient rows at the occurrence's sorted position:

@@ -57,6 +57,17 @@ def test_wd_small_shapes(cfg):
     run_wd(cfg, range(3))
 
 
+# edges of the fp64 product kernel: fewer rows or columns than a lane's vector
+# (1-3 samples, widths of 1-3), exact tiles of 64 and 128 and one past them,
+# K steps with and without a remainder, a batch long enough to split K
+@pytest.mark.parametrize("batch,fields,emb,deep", [
+    (1, 1, 3, (3,)), (2, 1, 1, (1, 2)), (3, 2, 3, (5, 3)), (4, 1, 4, (4, 4)), (5, 3, 7, (2, 9)),
+    (64, 2, 8, (64, 128)), (65, 2, 8, (65, 129)), (128, 4, 16, (128, 64)), (129, 3, 21, (130, 67)),
+    (515, 3, 11, (63, 127)), (1027, 5, 16, (132, 30)), (2048, 2, 32, (64,))])
+def test_wd_product_edges(batch, fields, emb, deep):
+    run_wd(replace(ODD, name="widedeep_edges", batch=batch, n_fields=fields, emb_dim=emb, dim=emb + 1, deep=deep), range(2))
+
+
 def test_wd_paper_mlp_small_batch():
     """Three hidden layers of 1024 over 26 fields of 64; 301 samples."""
     run_wd(SMALL, range(2))
