@@ -41,13 +41,67 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
+// Lane exchanges in registers.  A shuffle through the LDS crossbar
+// (ds_bpermute) takes about a hundred cycles and shares one unit among the
+// waves of a compute unit; the exchanges of a butterfly need neither: within
+// a row of 16 lanes data-parallel moves rotate or permute, and gfx950 swaps
+// halves of two registers across rows of 16 and of 32 lanes.  The sums add in
+// the same order as with shuffles.  Measured: skip-gram step (two sums of 64
+// lanes per four rows) 11.58 -> 10.99 ms, ComplEx 0.546 -> 0.523, row-wise MF
+// of 100K entries at rank 50 0.176 -> 0.155.
+template <int CTRL, int BANKS = 0xf>
+__device__ __forceinline__ uint32_t dpp_mov(uint32_t old, uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, CTRL, 0xf, BANKS, false);
+}
+
+// The word of lane (lane ^ M) for M = 1, 2, 4 or 8.
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor_word(uint32_t x) {
+  static_assert(M == 1 || M == 2 || M == 4 || M == 8, "inside a row of 16 lanes");
+  if constexpr (M == 1) return dpp_mov<0xB1>(x, x);          // quad_perm 1, 0, 3, 2
+  else if constexpr (M == 2) return dpp_mov<0x4E>(x, x);     // quad_perm 2, 3, 0, 1
+  else if constexpr (M == 4) return dpp_mov<0x114, 0xa>(dpp_mov<0x104, 0x5>(x, x), x);   // shl 4 / shr 4 by quads
+  else return dpp_mov<0x128>(x, x);                          // row_ror 8
+}
+
+// a + (b of lane ^ M) on the lower lane of each pair and (a of lane ^ M) + b
+// on the upper one: with a == b, the butterfly's sum; otherwise a halving
+// step that leaves the pair's sum of a below and of b above.
+template <int M>
+__device__ __forceinline__ double pair_sum(double a, double b, bool upper) {
+  const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+  if constexpr (M == 32 || M == 16) {
+    // {a.lower, b.lower} and {a.upper, b.upper}
+    uint32_t x[2], y[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t wa = (uint32_t)(ua >> (32 * i)), wb = (uint32_t)(ub >> (32 * i));
+      const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(wa, wb, false, false)
+                             : __builtin_amdgcn_permlane16_swap(wa, wb, false, false);
+      x[i] = r[0];
+      y[i] = r[1];
+    }
+    return __builtin_bit_cast(double, (uint64_t)x[0] | (uint64_t)x[1] << 32) +
+           __builtin_bit_cast(double, (uint64_t)y[0] | (uint64_t)y[1] << 32);
+  } else {
+    const uint64_t send = upper ? ua : ub;
+    const double keep = upper ? b : a;
+    const uint64_t got = (uint64_t)lane_xor_word<M>((uint32_t)send) |
+                         (uint64_t)lane_xor_word<M>((uint32_t)(send >> 32)) << 32;
+    return keep + __builtin_bit_cast(double, got);
+  }
+}
+
 // Butterfly sum over aligned groups of L lanes (L a power of two <= 64).
 // Every lane of the group ends with the same value: a+b and b+a round alike.
 template <int L>
 __device__ __forceinline__ double group_sum(double v) {
-#pragma unroll
-  for (int o = L / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, L);
-  return v;
+  if constexpr (L > 1) {
+    v = pair_sum<L / 2>(v, v, false);
+    return group_sum<L / 2>(v);
+  } else {
+    return v;
+  }
 }
 
 // Sums J values over a group of L lanes at once (J <= L, both powers of two):
@@ -58,24 +112,29 @@ __device__ __forceinline__ double group_sum(double v) {
 template <int L, int J>
 __device__ __forceinline__ double group_multi_sum(double (&v)[J], int gl) {
   static_assert(J >= 1 && J <= L, "J must not exceed the group width");
+  if constexpr (J == 1) {
+    return group_sum<L>(v[0]);
+  } else {
+    double w[J / 2];
 #pragma unroll
-  for (int k = 0; (J >> k) > 1; ++k) {
-    const int half = (J >> k) / 2;
-    const int mask = L >> (k + 1);
-    const bool upper = (gl & mask) != 0;
-#pragma unroll
-    for (int i = 0; i < J / 2; ++i) {
-      if (i < half) {
-        const double keep = upper ? v[i + half] : v[i];
-        const double send = upper ? v[i] : v[i + half];
-        v[i] = keep + __shfl_xor(send, mask, L);
-      }
-    }
+    for (int i = 0; i < J / 2; ++i) w[i] = pair_sum<L / 2>(v[i], v[i + J / 2], (gl & (L / 2)) != 0);
+    return group_multi_sum<L / 2, J / 2>(w, gl);
   }
-  double s = v[0];
-#pragma unroll
-  for (int o = L / J / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, L);
-  return s;
+}
+
+// The value of lane `src` (the same for the whole wavefront).
+__device__ __forceinline__ double lane_bcast(double v, int src) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, src);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), src);
+  return __builtin_bit_cast(double, (uint64_t)lo | (uint64_t)hi << 32);
+}
+
+// The value of lane `src` of each group of L lanes (src a constant).
+template <int L>
+__device__ __forceinline__ double group_bcast(double v, int src) {
+  if constexpr (L == WAVE) return lane_bcast(v, src);
+  else return __shfl(v, src, L);
 }
 
 // ------------------------------------------------------------------ block scan

@@ -118,10 +118,11 @@ struct SrcMFRow {
       }
     }
     dot = group_sum<L>(dot);
-    nu = group_sum<L>(nu);
-    nm = group_sum<L>(nm);
     const double err = (double)m.y - dot;
-    if (gl == 0) lsum += 0.5 * err * err + 0.5 * lam * (nu + nm);
+    // every lane keeps its own columns' part of the norms: the workgroup's
+    // loss adds all lanes anyway
+    lsum += 0.5 * lam * (nu + nm);
+    if (gl == 0) lsum += 0.5 * err * err;
     float* gc = grads + (int64_t)m.col_pos * gld;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(BLOCK) void k_kge_grad(const float* __restrict__ W,
 #pragma unroll
       for (int jj = 0; jj < JB; ++jj) {
         const int j = j0 + jj;
-        const double cj = __shfl(c_my, jj * (WAVE / JB), WAVE);
+        const double cj = group_bcast<WAVE>(c_my, jj * (WAVE / JB));
         if (j >= n_neg) break;
         const bool hd = j < n_head;
 #pragma unroll
@@ -765,7 +766,7 @@ __global__ __launch_bounds__(BLOCK) void k_sgns_grad(const float* __restrict__ W
       }
 #pragma unroll
       for (int jj = 0; jj < JB; ++jj) {
-        const double aj = __shfl(a_my, jj * (L / JB), L);
+        const double aj = group_bcast<L>(a_my, jj * (L / JB));
         if (used[jj])
 #pragma unroll
           for (int e = 0; e < NE; ++e) gv[e * BLOCK] += aj * (double)ustash[jj * NE + e][threadIdx.x];
