@@ -130,6 +130,14 @@ __device__ __forceinline__ double lane_bcast(double v, int src) {
   return __builtin_bit_cast(double, (uint64_t)lo | (uint64_t)hi << 32);
 }
 
+// The word of lane `src` of each group of L lanes (src the same for the
+// whole wavefront where L is the wavefront).
+template <int L>
+__device__ __forceinline__ uint32_t group_word(uint32_t x, int src) {
+  if constexpr (L == WAVE) return (uint32_t)__builtin_amdgcn_readlane((int)x, src);
+  else return __shfl(x, src, L);
+}
+
 // The value of lane `src` of each group of L lanes (src a constant).
 template <int L>
 __device__ __forceinline__ double group_bcast(double v, int src) {

@@ -69,6 +69,23 @@ ADAPM_HD inline double log1p_unit(double e) {
   return 2.0 * s * q;
 }
 
+// A double rounded to the 24 significant bits of an fp32 value, in integer
+// arithmetic: half of the last place is added and the bits below it cleared
+// (halfway cases go away from zero; infinities and NaN stay what they are; the
+// range stays a double's, so nothing overflows to infinity or loses bits as an
+// fp32 subnormal).  Going through an fp32 word and back costs two conversions,
+// each at a quarter of the fp64 rate.
+ADAPM_HD inline double round_to_24_bits(double p) {
+  constexpr unsigned long long HALF = 1ull << 28, BELOW = (1ull << 29) - 1;
+  return __builtin_bit_cast(double, (__builtin_bit_cast(unsigned long long, p) + HALF) & ~BELOW);
+}
+
+// sigmoid(x) = 1 / (1 + e^-x) from e = exp(-|x|), as below.
+ADAPM_HD inline double sigmoid(double x) {
+  const double e = exp_nonpos(-__builtin_fabs(x));
+  return (x >= 0.0 ? 1.0 : e) / (1.0 + e);
+}
+
 // sigmoid(x) = 1 / (1 + e^-x) and softplus(x) = log(1 + e^x) from one
 // e = exp(-|x|): sigmoid = (x >= 0 ? 1 : e) / (1 + e), softplus =
 // max(x, 0) + log(1 + e).

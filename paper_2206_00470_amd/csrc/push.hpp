@@ -7,6 +7,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "fp64math.hpp"
 
 namespace adapm {
 
@@ -123,23 +124,32 @@ __global__ __launch_bounds__(BLOCK) void k_gather_probe(const float* __restrict_
 // ------------------------------------------------------------------ gradient sources
 // A source describes the fp32 gradient row of the occurrence at sorted
 // position j in two steps:
-//   meta(j)            the per-occurrence indirections (loaded by one lane,
-//                      for up to L consecutive positions at once)
-//   load(m, own, ...)  the lane's fragment of the gradient row, given the
-//                      broadcast metadata and, for sources that need it
-//                      (kNeedsOwn), the pre-step row of the segment's key.
-// Metadata travels between lanes word by word.
-template <class T>
-__device__ __forceinline__ T shfl_pod(const T& v, int src, int width) {
-  static_assert(sizeof(T) % 4 == 0, "metadata must be whole words");
-  union U {
-    T t;
-    uint32_t w[sizeof(T) / 4];
-  } in, out;
-  in.t = v;
+//   meta(j)               the per-occurrence indirections (loaded by one lane,
+//                         for up to L consecutive positions at once)
+//   load(m, j, own, ...)  the lane's fragment of the gradient row, given the
+//                         broadcast metadata and, for sources that need it
+//                         (kNeedsOwn), the pre-step row of the segment's key.
+// Metadata travels between lanes word by word, and holds row indices, not
+// addresses: an address put together from exchanged words has lost its
+// address space, so its loads become flat ones, which count against the LDS
+// exchanges too and so made each of those wait for the row loads before it.
+// Where a row group is the whole wavefront the words are read into scalar
+// registers, which then hold the row's address as well.
+template <int L, class T>
+__device__ __forceinline__ T group_pod(const T& v, int src) {
+  if constexpr (std::is_empty_v<T>) {
+    return v;
+  } else {
+    static_assert(sizeof(T) % 4 == 0, "metadata must be whole words");
+    union U {
+      T t;
+      uint32_t w[sizeof(T) / 4];
+    } in, out;
+    in.t = v;
 #pragma unroll
-  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) out.w[i] = __shfl(in.w[i], src, width);
-  return out.t;
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) out.w[i] = group_word<L>(in.w[i], src);
+    return out.t;
+  }
 }
 
 // Gradient rows in occurrence order, ld floats apart, read through the sort
@@ -151,15 +161,16 @@ struct SrcIndirect {
   int dim;
   int64_t ld;
   struct Meta {
-    const float* row;
+    uint32_t row;
   };
-  __device__ __forceinline__ Meta meta(int64_t j) const { return {grads + (int64_t)perm[j] * ld}; }
+  __device__ __forceinline__ Meta meta(int32_t j) const { return {perm[j]}; }
   template <int L, int NV, int VW, bool NT>
-  __device__ __forceinline__ void load(const Meta& m, const float*, int gl, float* x) const {
+  __device__ __forceinline__ void load(const Meta& m, int32_t, const float*, int gl, float* x) const {
+    const float* row = grads + (int64_t)m.row * ld;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int c = (gl + v * L) * VW;
-      if (c < dim) load_row<VW, NT>(m.row + c, x + v * VW);
+      if (c < dim) load_row<VW, NT>(row + c, x + v * VW);
     }
   }
 };
@@ -170,16 +181,15 @@ struct SrcSorted {
   const float* grads;
   int dim;
   int64_t ld;
-  struct Meta {
-    const float* row;
-  };
-  __device__ __forceinline__ Meta meta(int64_t j) const { return {grads + j * ld}; }
+  struct Meta {};
+  __device__ __forceinline__ Meta meta(int32_t) const { return {}; }
   template <int L, int NV, int VW, bool NT>
-  __device__ __forceinline__ void load(const Meta& m, const float*, int gl, float* x) const {
+  __device__ __forceinline__ void load(const Meta&, int32_t j, const float*, int gl, float* x) const {
+    const float* row = grads + (int64_t)j * ld;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int c = (gl + v * L) * VW;
-      if (c < dim) load_row<VW, NT>(m.row + c, x + v * VW);
+      if (c < dim) load_row<VW, NT>(row + c, x + v * VW);
     }
   }
 };
@@ -193,11 +203,33 @@ constexpr bool src_has_loss() {
   else return false;
 }
 
+// Sources with kCoef = true give the gradient row as coefficient x row:
+// load returns the row (elements of type Src::Elem, float otherwise) and
+// m.coef scales it on its way into the sum, each product rounded to 24 bits
+// as a stored fp32 gradient row would be.  Conversions, not the gathers,
+// bounded the merges of coefficients: skip-gram's 17M occurrences of 300
+// floats took 5.2 ms with the products rounded through fp32 words and two
+// rows in flight, and take 3.1 ms with round_to_24_bits and four (8 TB/s of
+// rows read, most of them from the caches).
+template <class Src>
+constexpr bool src_has_coef() {
+  if constexpr (requires { Src::kCoef; }) return Src::kCoef;
+  else return false;
+}
+template <class Src> struct SrcElem { using type = float; };
+template <class Src> requires(src_has_coef<Src>()) struct SrcElem<Src> { using type = typename Src::Elem; };
+
+template <class Src, class T>
+__device__ __forceinline__ void add_element(double& acc, const typename Src::Meta& m, T x) {
+  if constexpr (src_has_coef<Src>()) acc += round_to_24_bits(m.coef * (double)x);
+  else acc += (double)x;
+}
+
 template <int L, int NV, int VW, bool NT, class Src>
-__device__ __forceinline__ void src_load(const Src& src, const typename Src::Meta& m, const float* own, int gl,
-                                         float* x, double& lsum) {
-  if constexpr (src_has_loss<Src>()) src.template load<L, NV, VW, NT>(m, own, gl, x, lsum);
-  else src.template load<L, NV, VW, NT>(m, own, gl, x);
+__device__ __forceinline__ void src_load(const Src& src, const typename Src::Meta& m, int32_t j, const float* own,
+                                         int gl, typename SrcElem<Src>::type* x, double& lsum) {
+  if constexpr (src_has_loss<Src>()) src.template load<L, NV, VW, NT>(m, j, own, gl, x, lsum);
+  else src.template load<L, NV, VW, NT>(m, j, own, gl, x);
 }
 
 // ------------------------------------------------------------------ reduce
@@ -243,8 +275,12 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
                                                      int part) {
   constexpr int GPB = BLOCK / L;
   constexpr int NE = NV * VW;
-  constexpr int UNROLL = src_has_loss<Src>() ? 1 : (NE <= 4 ? 4 : 2);
   using Meta = typename Src::Meta;
+  using Elem = typename SrcElem<Src>::type;
+  // rows in flight
+  constexpr int ROW_WORDS = NE * (int)(sizeof(Elem) / 4);
+  constexpr int UNROLL = src_has_loss<Src>() ? 1
+                       : src_has_coef<Src>() ? (sizeof(Elem) == 4 ? 4 : 2) : (ROW_WORDS <= 4 ? 4 : 2);
   const int gl = threadIdx.x % L;
   // part 0: every chunk; 1: chunks whose key reaches the split key; 2: the others
   int64_t cbeg = 0, cend = sv.hdr->num_chunks;
@@ -273,13 +309,13 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
     }
   for (int ci = 0; ci < ccount; ++ci) {
     const int64_t c = cb + ci * S;
-    const int64_t j0 = __shfl(my_j0, ci, L);
-    const int64_t j1 = __shfl(my_j1, ci, L);
-    const uint32_t key = __shfl(my_key, ci, L);
-    const uint32_t flags = __shfl(my_flags, ci, L);
+    const int32_t j0 = (int32_t)group_word<L>((uint32_t)my_j0, ci);
+    const int32_t j1 = (int32_t)group_word<L>((uint32_t)my_j1, ci);
+    const uint32_t key = group_word<L>(my_key, ci);
+    const uint32_t flags = group_word<L>(my_flags, ci);
     const bool head = flags & 1u;
     const bool whole = flags & 2u;
-    const Meta first = shfl_pod(my_first, ci, L);
+    const Meta first = group_pod<L>(my_first, ci);
     VT* wrow = W + (int64_t)key * ld;
     float* grow = G + (int64_t)key * gld;
     float wv[NE], gv[NE];
@@ -298,26 +334,31 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
     double acc[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) acc[e] = 0.0;
-    for (int64_t jb = j0; jb < j1; jb += L) {
-      const int cnt = (int)((j1 - jb) < L ? (j1 - jb) : L);
+    for (int32_t jb = j0; jb < j1; jb += L) {
+      const int cnt = j1 - jb < L ? j1 - jb : L;
       Meta mine{};
       if (jb == j0 && gl == 0) mine = first;            // prefetched with the chunk bounds
       else if (gl < cnt) mine = src.meta(jb + gl);
       int q = 0;
       for (; q + UNROLL <= cnt; q += UNROLL) {
-        float x[UNROLL][NE];
+        Elem x[UNROLL][NE];
+        Meta m[UNROLL];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) src_load<L, NV, VW, NT>(src, shfl_pod(mine, q + u, L), wv, gl, x[u], lsum);
+        for (int u = 0; u < UNROLL; ++u) {
+          m[u] = group_pod<L>(mine, q + u);
+          src_load<L, NV, VW, NT>(src, m[u], jb + q + u, wv, gl, x[u], lsum);
+        }
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u)
 #pragma unroll
-          for (int e = 0; e < NE; ++e) acc[e] += (double)x[u][e];
+          for (int e = 0; e < NE; ++e) add_element<Src>(acc[e], m[u], x[u][e]);
       }
       for (; q < cnt; ++q) {
-        float x[NE];
-        src_load<L, NV, VW, NT>(src, shfl_pod(mine, q, L), wv, gl, x, lsum);
+        Elem x[NE];
+        const Meta m = group_pod<L>(mine, q);
+        src_load<L, NV, VW, NT>(src, m, jb + q, wv, gl, x, lsum);
 #pragma unroll
-        for (int e = 0; e < NE; ++e) acc[e] += (double)x[e];
+        for (int e = 0; e < NE; ++e) add_element<Src>(acc[e], m, x[e]);
       }
     }
     if (whole && RW) {

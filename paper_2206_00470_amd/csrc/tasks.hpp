@@ -89,23 +89,24 @@ struct SrcMFRow {
   int dim;
   int64_t gld;   // row stride of grads
   struct Meta {
-    const VT* partner;
+    uint32_t col_key;
     float y;
     uint32_t col_pos;
   };
-  __device__ __forceinline__ Meta meta(int64_t j) const {
+  __device__ __forceinline__ Meta meta(int32_t j) const {
     const MFEntry r = pe[j];
-    return {W + (int64_t)r.col_key * ld, r.y, r.col_pos};
+    return {r.col_key, r.y, r.col_pos};
   }
   template <int L, int NV, int VW, bool NT>
-  __device__ __forceinline__ void load(const Meta& m, const float* own, int gl, float* x, double& lsum) const {
+  __device__ __forceinline__ void load(const Meta& m, int32_t, const float* own, int gl, float* x, double& lsum) const {
+    const VT* partner = W + (int64_t)m.col_key * ld;
     float p[NV * VW];
     double dot = 0.0, nu = 0.0, nm = 0.0;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int c = (gl + v * L) * VW;
       if (c < dim) {
-        load_vals<VW>(m.partner + c, p + v * VW);
+        load_vals<VW>(partner + c, p + v * VW);
 #pragma unroll
         for (int q = 0; q < VW; ++q) {
           // a product of two floats is exact in fp64, so a fused multiply-add
@@ -537,41 +538,49 @@ __global__ __launch_bounds__(BLOCK) void k_kge_grad(const float* __restrict__ W,
 // Gradient source of the KGE push.
 struct SrcKGE {
   static constexpr bool kNeedsOwn = false;
+  static constexpr bool kCoef = true;
+  using Elem = double;
   const uint32_t* perm;
   const float* mat;
   const double* base;
   const double* coef;
   int per, n_head, dim;
+  // the fp32 stored row (s, r, o), or with kBase the fp64 base row (negatives)
+  static constexpr uint32_t kBase = 1u << 31;
   struct Meta {
-    const void* row;    // fp32 stored row (s, r, o) or fp64 base row (negatives)
-    double c;           // coefficient of a negative
-    uint32_t scaled;    // 1: row is fp64 and scaled by c
+    double coef;        // of a negative; 1 for a stored row
+    uint32_t row;       // row of mat, or kBase + row of base (3 per triple, below 2^31)
     uint32_t pad;
   };
-  __device__ __forceinline__ Meta meta(int64_t j) const {
+  __device__ __forceinline__ Meta meta(int32_t j) const {
     const uint32_t occ = perm[j];
     const uint32_t t = occ / (uint32_t)per;
     const uint32_t q = occ - t * (uint32_t)per;
-    if (q < 3) return {mat + ((int64_t)t * 3 + q) * dim, 0.0, 0u, 0u};
-    return {base + ((int64_t)t * 2 + ((int)q - 3 < n_head ? 0 : 1)) * dim, coef[occ], 1u, 0u};
+    if (q < 3) return {1.0, t * 3 + q, 0u};
+    return {coef[occ], kBase + t * 2 + ((int)q - 3 < n_head ? 0u : 1u), 0u};
   }
   template <int L, int NV, int VW, bool NT>
-  __device__ __forceinline__ void load(const Meta& m, const float*, int gl, float* x) const {
-    if (!m.scaled) {
-      const float* row = static_cast<const float*>(m.row);
+  __device__ __forceinline__ void load(const Meta& m, int32_t, const float*, int gl, double* x) const {
+    if (!(m.row & kBase)) {
+      const float* row = mat + (int64_t)m.row * dim;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const int c = (gl + v * L) * VW;
-        if (c < dim) load_frag<VW>(row + c, x + v * VW);
+        if (c < dim) {
+          float t[VW];
+          load_frag<VW>(row + c, t);
+#pragma unroll
+          for (int e = 0; e < VW; ++e) x[v * VW + e] = t[e];
+        }
       }
     } else {
-      const double* row = static_cast<const double*>(m.row);
+      const double* row = base + (int64_t)(m.row - kBase) * dim;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const int c = (gl + v * L) * VW;
         if (c < dim)
 #pragma unroll
-          for (int e = 0; e < VW; ++e) x[v * VW + e] = (float)(m.c * row[c + e]);
+          for (int e = 0; e < VW; ++e) x[v * VW + e] = row[c + e];
       }
     }
   }
@@ -627,6 +636,14 @@ struct KeysSGNS {
 // softplus(-x)) and its negatives (a = sigmoid(x), loss softplus(x)).
 // Stores one fp64 coefficient a per output occurrence (its gradient row is
 // a*v) and the centre's fp32 gradient row sum(a*u).
+//
+// Bound by the gathers of the output rows: 17M rows of 1,200 bytes move at
+// 5.1 TB/s in 4.0 ms, and a kernel that only reads the same rows reaches 4.9.
+// Rows and sums stay in registers (parked in LDS, with the sums, around the
+// coefficients' transcendentals, the LDS was as busy as memory: 5.0 ms), the
+// fp32 words are converted a second time rather than held as doubles (206
+// registers, 4.2 ms), and the loss terms and the coefficients' stores wait
+// until every lane has a row of its own, once per L rows.
 template <int L, int NV, int VW>
 __global__ __launch_bounds__(BLOCK) void k_sgns_grad(const float* __restrict__ W, int64_t ld, int dim,
                                                      const int32_t* __restrict__ centre,
@@ -637,28 +654,27 @@ __global__ __launch_bounds__(BLOCK) void k_sgns_grad(const float* __restrict__ W
                                                      double* __restrict__ loss_part) {
   constexpr int GPB = BLOCK / L;
   constexpr int NE = NV * VW;
-  constexpr int JB = L >= 4 ? 4 : L;   // output rows scored together (power of two <= L)
+  constexpr int JB = 4;        // output rows scored together
+  constexpr int PER = L / JB;  // lanes that end up with the same row's score; batches in a tile of L rows
   __shared__ double sm[WAVES_PER_BLOCK];
-  __shared__ float ustash[JB * NE][BLOCK];   // one batch of rows, lane-major
-  __shared__ double gacc[NE][BLOCK];
   const int gl = threadIdx.x % L;
   const int64_t per = 1 + (int64_t)slots * (K + 1);
   double lsum = 0.0;
   for (int64_t b = (int64_t)blockIdx.x * GPB + threadIdx.x / L; b < B; b += (int64_t)gridDim.x * GPB) {
     if (!ok[b]) continue;
     const float* vp = W + (int64_t)centre[b] * ld;
-    float v[NE];
-    double* gv = gacc[0] + threadIdx.x;   // gv[e] is gacc[e][thread]: the centre gradient in fp64
+    double v[NE], gv[NE];   // the centre's row and its gradient
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
       const int c = (gl + q * L) * VW;
-      if (c < dim) load_frag<VW>(vp + c, v + q * VW);
-      else
+      float t[VW] = {};
+      if (c < dim) load_frag<VW>(vp + c, t);
 #pragma unroll
-        for (int e = 0; e < VW; ++e) v[q * VW + e] = 0.0f;
+      for (int e = 0; e < VW; ++e) {
+        v[q * VW + e] = t[e];
+        gv[q * VW + e] = 0.0;
+      }
     }
-#pragma unroll
-    for (int e = 0; e < NE; ++e) gv[e * BLOCK] = 0.0;
     // the output rows of the centre's present slots in occurrence order: row
     // r is slot r / (K+1), position r % (K+1) (0 = the context word, then the
     // negatives).  The loop runs over "live" rows rp, the rows of present
@@ -666,8 +682,10 @@ __global__ __launch_bounds__(BLOCK) void k_sgns_grad(const float* __restrict__ W
     // through a bit mask of the present slots (up to 64 slots; with more,
     // every slot is visited and absent ones are skipped row by row).  Lane i
     // holds the table id of live row t*L + i of the current tile t of L rows
-    // (-1: absent or past the end); the next tile's ids are loaded one tile
-    // ahead, so the row loads never wait for an id load.
+    // (kNone: absent or past the end; kCtx set on context words); the next
+    // tile's ids are loaded one tile ahead, so the row loads never wait for
+    // an id load.
+    constexpr uint32_t kNone = 0xffffffffu, kCtx = 1u << 31;   // ids are below 2^31 - 1
     uint64_t present = 0;
     bool compact = false;   // some slot absent, and at most 64 slots
     if (slots <= 64) {
@@ -682,94 +700,97 @@ __global__ __launch_bounds__(BLOCK) void k_sgns_grad(const float* __restrict__ W
       for (int i = 0; i < nth; ++i) m &= m - 1;   // drop the nth lowest present slots
       return __builtin_ctzll(m) * (K + 1) + (rp - nth * (K + 1));
     };
-    // table id of live row rp (-1: absent or past the end) and its row r
-    auto row_id = [&](int rp, int& r) -> int64_t {
+    auto row_id = [&](int rp, int& r) -> uint32_t {   // id of live row rp, and its row r
       r = 0;
-      if (rp >= rows) return -1;
+      if (rp >= rows) return kNone;
       r = map_row(rp);
       const int q = r / (K + 1);
       const int k = r - q * (K + 1);
-      const int64_t cx = ctx[b * slots + q];
-      const int64_t ng = k == 0 ? 0 : (int64_t)neg[(b * slots + q) * K + (k - 1)];
-      return cx == -1 ? -1 : (k == 0 ? cx : ng);
+      const int32_t cx = ctx[b * slots + q];
+      if (cx == -1) return kNone;
+      return k == 0 ? kCtx | (uint32_t)cx : (uint32_t)neg[(b * slots + q) * K + (k - 1)];
     };
     int r_cur, r_nxt;
-    int64_t id_cur = row_id(gl, r_cur);
-    int64_t id_nxt = row_id(L + gl, r_nxt);
+    uint32_t id_cur = row_id(gl, r_cur);
+    uint32_t id_nxt = row_id(L + gl, r_nxt);
     // the rows of live rows rb .. rb + JB - 1 (rb a multiple of JB, inside
-    // the id tile held in id_cur)
+    // the id tile held in id_cur); absent ones read as zero
     float u[JB][NE];
-    bool live[JB];
     auto load_batch = [&](int rb) {
 #pragma unroll
       for (int jj = 0; jj < JB; ++jj) {
-        const int64_t id = __shfl(id_cur, rb % L + jj, L);
-        live[jj] = id != -1;
-        const float* up = W + (out_off + (live[jj] ? id : 0)) * ld;
+        const uint32_t id = group_word<L>(id_cur, rb % L + jj);
+        const float* up = W + (out_off + (int64_t)(id & ~kCtx)) * ld;
 #pragma unroll
         for (int q2 = 0; q2 < NV; ++q2) {
           const int c = (gl + q2 * L) * VW;
-          if (c < dim) load_frag<VW>(up + c, u[jj] + q2 * VW);
+          if (id != kNone && c < dim) load_frag<VW>(up + c, u[jj] + q2 * VW);
           else
 #pragma unroll
             for (int e = 0; e < VW; ++e) u[jj][q2 * VW + e] = 0.0f;
         }
       }
     };
+    // score and coefficient of one row of the tile per lane: lane gl keeps
+    // those of row JB * (gl % PER) + gl / PER, so that the loss terms and the
+    // coefficients' stores are done once per tile, by all lanes
+    double x_keep = 0.0, a_keep = 0.0;
+    auto finish_tile = [&]() {
+      const int src = JB * (gl % PER) + gl / PER;
+      const bool live = __shfl(id_cur, src, L) != kNone;
+      const int r = __shfl(r_cur, src, L);
+      double sig, sp;
+      sigmoid_softplus(x_keep, &sig, &sp);
+      if (live) {
+        lsum += sp;
+        coef[b * per + 1 + r] = a_keep;
+      }
+    };
     if (rows > 0) load_batch(0);
     for (int r0 = 0; r0 < rows; r0 += JB) {
       double x[JB];
 #pragma unroll
-      for (int e = 0; e < NE; ++e) asm volatile("" : "+v"(v[e]));   // convert v per batch, not once for the loop
-#pragma unroll
       for (int jj = 0; jj < JB; ++jj) {
         double p = 0.0;
 #pragma unroll
-        for (int e = 0; e < NE; ++e) p = __builtin_fma((double)u[jj][e], (double)v[e], p);   // exact product
+        for (int e = 0; e < NE; ++e) p = __builtin_fma((double)u[jj][e], v[e], p);   // exact product
         x[jj] = p;
       }
-      // park the rows in LDS while the coefficients are computed (the fp64
-      // transcendentals need many registers; the rows come back for the update)
+      float cur[JB][NE];
 #pragma unroll
       for (int jj = 0; jj < JB; ++jj)
 #pragma unroll
-        for (int e = 0; e < NE; ++e) ustash[jj * NE + e][threadIdx.x] = u[jj][e];
-      // lane finishes the score of live row r0 + gl / (L / JB) and its coefficient
+        for (int e = 0; e < NE; ++e) {
+          cur[jj][e] = u[jj][e];
+          asm volatile("" : "+v"(cur[jj][e]));   // hold fp32 words across the sigmoid, convert them again below
+        }
+      // lane finishes the score of live row r0 + gl / PER and its coefficient:
+      // context word: a = -sigmoid(-x), loss softplus(-x); negative: a = sigmoid(x), loss softplus(x)
       const double x_my = group_multi_sum<L, JB>(x, gl);
-      const bool live_my = __shfl(id_cur, r0 % L + gl / (L / JB), L) != -1;   // also false past the end
-      const int r_my = __shfl(r_cur, r0 % L + gl / (L / JB), L);
-      bool used[JB];
-#pragma unroll
-      for (int jj = 0; jj < JB; ++jj) used[jj] = live[jj];
-      // the next batch's rows load while this batch's coefficients are formed
+      const uint32_t id_my = __shfl(id_cur, r0 % L + gl / PER, L);
+      const bool last = (r0 + JB) % L == 0 || r0 + JB >= rows;   // of its tile
+      const double sgn = id_my & kCtx ? -1.0 : 1.0;
+      const double sx = sgn * x_my;
+      const double a_my = sgn * sigmoid(sx);
+      if (gl % PER == r0 % L / JB) {
+        x_keep = sx;
+        a_keep = a_my;
+      }
+      if (last) finish_tile();
+      // the next batch's rows load while this batch's rows are added
       if (r0 + JB < rows) {
-        if ((r0 + JB) % L == 0) {
+        if (last) {
           id_cur = id_nxt;
           r_cur = r_nxt;
           id_nxt = row_id(r0 + JB + L + gl, r_nxt);
         }
         load_batch(r0 + JB);
       }
-      double a_my = 0.0;
-      if (live_my) {
-        const int q_my = r_my / (K + 1);
-        const int k_my = r_my - q_my * (K + 1);
-        // context word: a = -sigmoid(-x), loss softplus(-x); negative: a = sigmoid(x), loss softplus(x)
-        const double sgn = k_my == 0 ? -1.0 : 1.0;
-        double sig, sp;
-        sigmoid_softplus(sgn * x_my, &sig, &sp);
-        a_my = sgn * sig;
-        if (gl % (L / JB) == 0) {
-          lsum += sp;
-          coef[b * per + 1 + r_my] = a_my;
-        }
-      }
 #pragma unroll
       for (int jj = 0; jj < JB; ++jj) {
-        const double aj = group_bcast<L>(a_my, jj * (L / JB));
-        if (used[jj])
+        const double aj = group_bcast<L>(a_my, jj * PER);
 #pragma unroll
-          for (int e = 0; e < NE; ++e) gv[e * BLOCK] += aj * (double)ustash[jj * NE + e][threadIdx.x];
+        for (int e = 0; e < NE; ++e) gv[e] = __builtin_fma(aj, (double)cur[jj][e], gv[e]);   // an absent row is zero
       }
     }
     float* dst = mat + b * dim;
@@ -779,7 +800,7 @@ __global__ __launch_bounds__(BLOCK) void k_sgns_grad(const float* __restrict__ W
       if (c < dim) {
         float g[VW];
 #pragma unroll
-        for (int e = 0; e < VW; ++e) g[e] = (float)gv[(q * VW + e) * BLOCK];
+        for (int e = 0; e < VW; ++e) g[e] = (float)gv[q * VW + e];
         store_frag<VW>(dst + c, g);
       }
     }
@@ -793,6 +814,8 @@ __global__ __launch_bounds__(BLOCK) void k_sgns_grad(const float* __restrict__ W
 // row, read from the table before the input rows are updated.
 struct SrcSGNS {
   static constexpr bool kNeedsOwn = false;
+  static constexpr bool kCoef = true;
+  using Elem = float;
   const uint32_t* perm;
   const float* mat;
   const double* coef;
@@ -800,30 +823,28 @@ struct SrcSGNS {
   const float* W;
   int64_t ld;
   int per, dim;
+  // the centre's input row (key below 2^31), or with kStored its stored
+  // gradient row
+  static constexpr uint32_t kStored = 1u << 31;
   struct Meta {
-    const float* row;   // the centre's stored gradient row, or its input row
-    double a;           // coefficient of an output occurrence
-    uint32_t scaled;    // 1: row is the input row, scaled by a
+    double coef;        // of an output occurrence; 1 for a stored row
+    uint32_t row;       // row of W, or kStored + row of mat
     uint32_t pad;
   };
-  __device__ __forceinline__ Meta meta(int64_t j) const {
+  __device__ __forceinline__ Meta meta(int32_t j) const {
     const uint32_t occ = perm[j];
     const uint32_t b = occ / (uint32_t)per;
     const uint32_t q = occ - b * (uint32_t)per;
-    if (q == 0) return {mat + (int64_t)b * dim, 1.0, 0u, 0u};
-    return {W + (int64_t)centre[b] * ld, coef[occ], 1u, 0u};
+    if (q == 0) return {1.0, kStored + b, 0u};
+    return {coef[occ], (uint32_t)centre[b], 0u};
   }
   template <int L, int NV, int VW, bool NT>
-  __device__ __forceinline__ void load(const Meta& m, const float*, int gl, float* x) const {
+  __device__ __forceinline__ void load(const Meta& m, int32_t, const float*, int gl, float* x) const {
+    const float* row = m.row & kStored ? mat + (int64_t)(m.row - kStored) * dim : W + (int64_t)m.row * ld;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int c = (gl + v * L) * VW;
-      if (c < dim) {
-        float t[VW];
-        load_frag<VW>(m.row + c, t);
-#pragma unroll
-        for (int e = 0; e < VW; ++e) x[v * VW + e] = m.scaled ? (float)(m.a * (double)t[e]) : t[e];
-      }
+      if (c < dim) load_frag<VW>(row + c, x + v * VW);
     }
   }
 };
