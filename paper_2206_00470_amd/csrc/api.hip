@@ -454,6 +454,60 @@ ps_status run_segments(const SortBufs& b, const uint32_t* ks, int64_t n, int64_t
   });
 }
 
+// The key work of a call: sort and segments, by one workgroup where the keys
+// fit it (k_small_keys), else by the kernels above.  seg_off, uniq64 and
+// split_key as for run_segments, the rest as for run_sort.
+template <class KS>
+ps_status run_keywork(ps_store* s, KS ks, int64_t n, int64_t num_keys, SortBufs& b, int32_t* err, uint32_t* perm_out,
+                      bool want_rank, hipStream_t st, uint32_t** keys_sorted, uint32_t** perm, bool header_cleared,
+                      int32_t* seg_off, int64_t* uniq64, uint32_t split_key = 0) {
+  if (n > MID_KEYS_MAX) {
+    if (ps_status r = run_sort(s, ks, n, num_keys, b, err, perm_out, want_rank, st, keys_sorted, perm, header_cleared))
+      return r;
+    return run_segments(b, *keys_sorted, n, num_keys, seg_off, uniq64, st, split_key);
+  }
+  const RadixPlan plan = radix_plan(num_keys);
+  *keys_sorted = b.k[plan.passes % 2];   // where run_sort leaves them
+  *perm = perm_out ? perm_out : b.v[plan.passes % 2];
+  const SmallOut out{*keys_sorted, *perm, want_rank ? b.rank : nullptr, b.hdr, seg_off, uniq64, b.chunk_start, b.chunk_seg};
+  auto launch = [&](auto kernel) -> ps_status {
+    Timed t(s, PS_KERNEL_SCATTER, st);
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(SMALL_BLOCK), 0, st, ks, (int)n, (uint32_t)num_keys, plan, split_key, out,
+                       err);
+    LAUNCHED(k_small_keys);
+    return PS_OK;
+  };
+  if (n > SMALL_KEYS_MAX) {
+    const int tiles = (int)ceil_div(n, MID_TILE);
+    const uint32_t sentinel = (uint32_t)num_keys;
+    hipLaunchKernelGGL((k_mid_intake<KS>), dim3(tiles), dim3(SMALL_BLOCK), 0, st, ks, (int)n, sentinel, plan.bits[0],
+                       b.k[0], b.counts, err);
+    LAUNCHED(k_mid_intake);
+    for (int p = 0; p < plan.passes; ++p) {
+      const bool last = p == plan.passes - 1;
+      if (p > 0) {
+        hipLaunchKernelGGL(k_mid_count, dim3(tiles), dim3(SMALL_BLOCK), 0, st, b.k[p % 2], (int)n, plan.shift[p],
+                           plan.bits[p], b.counts);
+        LAUNCHED(k_mid_count);
+      }
+      Timed t(s, PS_KERNEL_SCATTER, st);
+      hipLaunchKernelGGL(k_mid_scatter, dim3(tiles), dim3(SMALL_BLOCK), 0, st, b.k[p % 2],
+                         p > 0 ? b.v[p % 2] : nullptr, (int)n, plan.shift[p], plan.bits[p], b.counts, tiles,
+                         b.k[1 - p % 2], last ? *perm : b.v[1 - p % 2], last && want_rank ? b.rank : nullptr);
+      LAUNCHED(k_mid_scatter);
+    }
+    hipLaunchKernelGGL(k_mid_seg_count, dim3(tiles), dim3(SMALL_BLOCK), 0, st, *keys_sorted, (int)n, sentinel, b.tstat);
+    LAUNCHED(k_mid_seg_count);
+    hipLaunchKernelGGL(k_mid_seg_write, dim3(tiles), dim3(SMALL_BLOCK), 0, st, *keys_sorted, (int)n, sentinel, b.tstat,
+                       tiles, split_key, b.hdr, seg_off, uniq64, b.chunk_start, b.chunk_seg);
+    LAUNCHED(k_mid_seg_write);
+    return PS_OK;
+  }
+  if (n <= SMALL_BLOCK) return launch(k_small_keys<KS, 1>);
+  if (n <= 4 * SMALL_BLOCK) return launch(k_small_keys<KS, 4>);
+  return launch(k_small_keys<KS, SMALL_ITEMS_MAX>);
+}
+
 // The skip-gram gradient kernel's lane layout.  For rows of 257..384 floats
 // (300 in the paper's word vectors) float4 fragments would fill 64 lanes
 // twice with most of the second pass idle (75 vectors for dim 300); float2
@@ -666,9 +720,10 @@ ps_status mf_prepare(ps_store* s, const int32_t* row, const int32_t* col, const 
   const int64_t n = 2 * B;
   uint32_t *ks, *perm;
   KeysMF kmf{row, col, col_key_offset, s->num_keys};
-  if (ps_status r = run_sort(s, kmf, n, s->num_keys, p.sb, s->status, nullptr, true, st, &ks, &perm)) return r;
   const uint32_t split = (uint32_t)(col_key_offset < s->num_keys ? col_key_offset : s->num_keys);
-  if (ps_status r = run_segments(p.sb, ks, n, s->num_keys, p.sb.seg_off, nullptr, st, split)) return r;
+  if (ps_status r = run_keywork(s, kmf, n, s->num_keys, p.sb, s->status, nullptr, true, st, &ks, &perm, false,
+                                p.sb.seg_off, nullptr, split))
+    return r;
   Timed t(s, PS_KERNEL_TASKGRAD, st);
   hipLaunchKernelGGL(k_mf_pack, dim3(small_grid(B, BLOCK, MERGE_GRID_MAX)), dim3(BLOCK), 0, st, row, col, val, B,
                      col_key_offset, s->num_keys, p.sb.rank, p.pe);
@@ -1288,9 +1343,8 @@ ps_status ps_pull(ps_store* s, const int64_t* keys, int64_t n, float* out, void*
 // only) and the merge of the gradient rows into the table.
 static ps_status push_prepare(ps_store* s, const int64_t* keys, int64_t n, Plan& p, hipStream_t st) {
   uint32_t *ks, *perm;
-  if (ps_status r = run_sort(s, KeysInt64{keys}, n, s->num_keys, p.sb, s->status, nullptr, false, st, &ks, &perm))
-    return r;
-  return run_segments(p.sb, ks, n, s->num_keys, p.sb.seg_off, nullptr, st);
+  return run_keywork(s, KeysInt64{keys}, n, s->num_keys, p.sb, s->status, nullptr, false, st, &ks, &perm, false,
+                     p.sb.seg_off, nullptr);
 }
 
 static ps_status push_apply(ps_store* s, int64_t n, const float* grads, Plan& p, hipStream_t st) {
@@ -1379,10 +1433,9 @@ ps_status ps_dedup(int64_t num_keys, const int64_t* keys, int64_t n, int64_t* un
   plan_op(ws, num_keys, 1, PS_OP_DEDUP, n, 1, &p);
   if (ps_status r = check_ws(p, ws, ws_bytes)) return r;
   uint32_t *ks, *pm;
-  if (ps_status r = run_sort(nullptr, KeysInt64{keys}, n, num_keys, p.sb, err, reinterpret_cast<uint32_t*>(perm),
-                             false, st, &ks, &pm))
+  if (ps_status r = run_keywork(nullptr, KeysInt64{keys}, n, num_keys, p.sb, err, reinterpret_cast<uint32_t*>(perm),
+                                false, st, &ks, &pm, false, offsets, uniq))
     return r;
-  if (ps_status r = run_segments(p.sb, ks, n, num_keys, offsets, uniq, st)) return r;
   HIP_TRY(hipMemcpyAsync(num_unique, &p.sb.hdr->num_unique, sizeof(int32_t), hipMemcpyDeviceToDevice, st));
   return PS_OK;
 }
@@ -1467,9 +1520,8 @@ static ps_status kge_keywork(ps_store* s, const int32_t* head, const int32_t* re
   const int per = 3 + n_neg;
   uint32_t *ks, *perm;
   KeysKGE kk{head, rel, tail, neg, per, n_neg, rel_key_offset, p.ok};
-  if (ps_status r = run_sort(s, kk, B * per, s->num_keys, p.sb, s->status, nullptr, false, st, &ks, &perm, true))
-    return r;
-  return run_segments(p.sb, ks, B * per, s->num_keys, p.sb.seg_off, nullptr, st);
+  return run_keywork(s, kk, B * per, s->num_keys, p.sb, s->status, nullptr, false, st, &ks, &perm, true, p.sb.seg_off,
+                     nullptr);
 }
 
 static ps_status kge_valid(ps_store* s, const int32_t* head, const int32_t* rel, const int32_t* tail,
@@ -1597,9 +1649,8 @@ static ps_status sgns_keywork(ps_store* s, const int32_t* centre, const int32_t*
   const int64_t per = 1 + (int64_t)slots * (1 + n_neg);
   uint32_t *ks, *perm;
   KeysSGNS kk{centre, ctx, neg, (int)per, slots, n_neg, out_key_offset, p.ok};
-  if (ps_status r = run_sort(s, kk, B * per, s->num_keys, p.sb, s->status, nullptr, false, st, &ks, &perm, true))
-    return r;
-  return run_segments(p.sb, ks, B * per, s->num_keys, p.sb.seg_off, nullptr, st, (uint32_t)out_key_offset);
+  return run_keywork(s, kk, B * per, s->num_keys, p.sb, s->status, nullptr, false, st, &ks, &perm, true, p.sb.seg_off,
+                     nullptr, (uint32_t)out_key_offset);
 }
 
 // Launches the gradient kernel; *grid receives its number of loss partials.
@@ -1689,10 +1740,8 @@ ps_status ps_step_sgns_apply(ps_store* s, const int32_t* centre, const int32_t* 
 // and the merge of those rows.
 static ps_status ctr_keywork(ps_store* s, const int64_t* keys, int64_t B, int32_t F, Plan& p, hipStream_t st) {
   uint32_t *ks, *perm;
-  if (ps_status r = run_sort(s, KeysCTR{keys, F, p.ok}, B * F, s->num_keys, p.sb, s->status, nullptr, false, st, &ks,
-                             &perm, true))
-    return r;
-  return run_segments(p.sb, ks, B * F, s->num_keys, p.sb.seg_off, nullptr, st);
+  return run_keywork(s, KeysCTR{keys, F, p.ok}, B * F, s->num_keys, p.sb, s->status, nullptr, false, st, &ks, &perm,
+                     true, p.sb.seg_off, nullptr);
 }
 
 static ps_status ctr_valid(ps_store* s, const int64_t* keys, int64_t B, int32_t F, Plan& p, hipStream_t st) {
@@ -1996,10 +2045,9 @@ ps_status ps_step_ctr_wd(ps_store* s, const int64_t* keys, const float* label, i
   // the key sort and segments run beside the MLP on the store's second stream
   if (ps_status r = fork_aux(s, st)) return r;
   uint32_t *ks, *perm;
-  if (ps_status r = run_sort(s, KeysCTR{keys, F, p.base.ok}, n, s->num_keys, p.base.sb, s->status, nullptr, true,
-                             s->aux, &ks, &perm, true))
+  if (ps_status r = run_keywork(s, KeysCTR{keys, F, p.base.ok}, n, s->num_keys, p.base.sb, s->status, nullptr, true,
+                                s->aux, &ks, &perm, true, p.base.sb.seg_off, nullptr))
     return r;
-  if (ps_status r = run_segments(p.base.sb, ks, n, s->num_keys, p.base.sb.seg_off, nullptr, s->aux)) return r;
   // inputs
   RowShape shape;
   row_shape(E, E % 4 == 0 && s->ld % 4 == 0, &shape);
