@@ -1314,23 +1314,32 @@ ps_status ps_pull(ps_store* s, const int64_t* keys, int64_t n, float* out, void*
   if (n == 0) return PS_OK;
   if (!keys || !out) return fail(PS_ERR_INVALID, "keys or out is NULL");
   hipStream_t st = as_stream(stream);
+  // the L2s hold 32 MB together: a larger output is not there any more when
+  // the caller reads it, a smaller one may be
+  const bool nt = n * s->dim * 4 > (int64_t(32) << 20);
   // rows of up to ROW_MAX floats in one pass; wider rows one column slice at a time
   for (int64_t col0 = 0; col0 < s->dim; col0 += ROW_MAX) {
     const int dim = (int)std::min<int64_t>(ROW_MAX, s->dim - col0);
     RowShape shape;
     row_shape(dim, aligned16(out) && s->dim % 4 == 0, &shape);
     ps_status r = with_shape(shape, [&]<int L, int NV, int VW>() -> ps_status {
-      int64_t grid = ceil_div(n, BLOCK / L);
+      int64_t grid = ceil_div(n, int64_t(PULL_ROWS<NV * VW>) * (BLOCK / L));
       if (grid > 65536) grid = 65536;
       Timed t(s, PS_KERNEL_PULL, st);
-      if (s->bf16)
-        hipLaunchKernelGGL((k_pull<L, NV, VW, bf16_t>), dim3(grid), dim3(BLOCK), 0, st,
-                           reinterpret_cast<const bf16_t*>(s->W) + col0, s->ld, s->num_keys, dim, keys, n,
-                           out + col0, (int64_t)s->dim, s->status, (const int32_t*)nullptr, int64_t(0));
-      else
-        hipLaunchKernelGGL((k_pull<L, NV, VW, float>), dim3(grid), dim3(BLOCK), 0, st, s->W + col0, s->ld,
-                           s->num_keys, dim, keys, n, out + col0, (int64_t)s->dim, s->status,
-                           s->stg ? s->stg->map : nullptr, s->stg ? s->stg->num_keys : int64_t(0));
+      auto launch = [&](auto kernel, auto values) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(BLOCK), 0, st, values + col0, s->ld, s->num_keys, dim, keys, n,
+                           out + col0, (int64_t)s->dim, s->status, s->stg ? s->stg->map : nullptr,
+                           s->stg ? s->stg->num_keys : int64_t(0));
+      };
+      if (s->bf16) {
+        const bf16_t* values = reinterpret_cast<const bf16_t*>(s->W);
+        if (nt) launch(k_pull<L, NV, VW, bf16_t, true>, values);
+        else launch(k_pull<L, NV, VW, bf16_t, false>, values);
+      } else {
+        const float* values = s->W;
+        if (nt) launch(k_pull<L, NV, VW, float, true>, values);
+        else launch(k_pull<L, NV, VW, float, false>, values);
+      }
       LAUNCHED(k_pull);
       return PS_OK;
     });
