@@ -512,7 +512,7 @@ ps_status run_keywork(ps_store* s, KS ks, int64_t n, int64_t num_keys, SortBufs&
 // (300 in the paper's word vectors) float4 fragments would fill 64 lanes
 // twice with most of the second pass idle (75 vectors for dim 300); float2
 // fragments three times fill 78% of the lanes and need a quarter fewer
-// registers and LDS per lane (measured 9-11% faster).  Other widths use the
+// registers per lane (measured 9-11% faster).  Other widths use the
 // common layout.
 template <class F>
 ps_status with_sgns_shape(int dim, int64_t ld, F&& f) {
