@@ -771,7 +771,9 @@ __global__ __launch_bounds__(BLOCK) void k_sgns_grad(const float* __restrict__ W
       const bool last = (r0 + JB) % L == 0 || r0 + JB >= rows;   // of its tile
       const double sgn = id_my & kCtx ? -1.0 : 1.0;
       const double sx = sgn * x_my;
-      const double a_my = sgn * sigmoid(sx);
+      // none for an absent row: with an infinite or NaN centre its score is a
+      // NaN (0 x inf), which its zeros would carry into the gradient
+      const double a_my = id_my == kNone ? 0.0 : sgn * sigmoid(sx);
       if (gl % PER == r0 % L / JB) {
         x_keep = sx;
         a_keep = a_my;
@@ -790,7 +792,7 @@ __global__ __launch_bounds__(BLOCK) void k_sgns_grad(const float* __restrict__ W
       for (int jj = 0; jj < JB; ++jj) {
         const double aj = group_bcast<L>(a_my, jj * PER);
 #pragma unroll
-        for (int e = 0; e < NE; ++e) gv[e] = __builtin_fma(aj, (double)cur[jj][e], gv[e]);   // an absent row is zero
+        for (int e = 0; e < NE; ++e) gv[e] = __builtin_fma(aj, (double)cur[jj][e], gv[e]);   // an absent row adds 0 x 0
       }
     }
     float* dst = mat + b * dim;
