@@ -230,12 +230,16 @@ constexpr bool src_has_loss() {
 
 // Sources with kCoef = true give the gradient row as coefficient x row:
 // load returns the row (elements of type Src::Elem, float otherwise) and
-// m.coef scales it on its way into the sum, each product rounded to 24 bits
-// as a stored fp32 gradient row would be.  Conversions, not the gathers,
-// bounded the merges of coefficients: skip-gram's 17M occurrences of 300
-// floats took 5.2 ms with the products rounded through fp32 words and two
-// rows in flight, and take 3.1 ms with round_to_24_bits and four (8 TB/s of
-// rows read, most of them from the caches).
+// m.coef scales it on its way into the sum, each product rounded as a stored
+// fp32 gradient row would be.  Conversions, not the gathers, bounded the merge
+// of skip-gram's coefficients x fp32 rows: 17M occurrences of 300 floats took
+// 5.2 ms with the products rounded through fp32 words and two rows in flight,
+// and take 3.1 ms with round_to_24_bits and four (6.6 TB/s of rows read, most
+// of them from the caches).  Its coefficients are at most 1 in magnitude (a
+// logistic function), so the products stay in the fp32 range.  A product with
+// an fp64 row (ComplEx: a product of two fp32 rows) may leave that range and is
+// then infinite, as a stored row is: those are converted, which costs nothing
+// measurable there (a step of 422K occurrences of 256 floats 524 us either way).
 template <class Src>
 constexpr bool src_has_coef() {
   if constexpr (requires { Src::kCoef; }) return Src::kCoef;
@@ -246,8 +250,9 @@ template <class Src> requires(src_has_coef<Src>()) struct SrcElem<Src> { using t
 
 template <class Src, class T>
 __device__ __forceinline__ void add_element(double& acc, const typename Src::Meta& m, T x) {
-  if constexpr (src_has_coef<Src>()) acc += round_to_24_bits(m.coef * (double)x);
-  else acc += (double)x;
+  if constexpr (!src_has_coef<Src>()) acc += (double)x;
+  else if constexpr (std::is_same_v<T, float>) acc += round_to_24_bits(m.coef * (double)x);
+  else acc += (double)(float)(m.coef * x);
 }
 
 template <int L, int NV, int VW, bool NT, class Src>
