@@ -19,6 +19,7 @@
 #include "common.hpp"
 #include "mlp.hpp"
 #include "push.hpp"
+#include "rules.hpp"
 #include "sort.hpp"
 #include "staging.hpp"
 #include "tasks.hpp"
@@ -1314,9 +1315,7 @@ ps_status ps_pull(ps_store* s, const int64_t* keys, int64_t n, float* out, void*
   if (n == 0) return PS_OK;
   if (!keys || !out) return fail(PS_ERR_INVALID, "keys or out is NULL");
   hipStream_t st = as_stream(stream);
-  // the L2s hold 32 MB together: a larger output is not there any more when
-  // the caller reads it, a smaller one may be
-  const bool nt = n * s->dim * 4 > (int64_t(32) << 20);
+  const bool nt = pull_streams(n, s->dim);
   // rows of up to ROW_MAX floats in one pass; wider rows one column slice at a time
   for (int64_t col0 = 0; col0 < s->dim; col0 += ROW_MAX) {
     const int dim = (int)std::min<int64_t>(ROW_MAX, s->dim - col0);

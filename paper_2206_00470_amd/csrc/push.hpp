@@ -26,10 +26,11 @@ struct RowShape {
 // width when a wide row is pulled in column slices).
 // Bound by the row reads and writes.  A group keeps PULL_ROWS rows in flight,
 // since one load per lane left it waiting for key, row and store in turn, and
-// NT (an output larger than the L2s together, see the launch) writes past the
-// caches.  Measured: 213K rows of 256 bytes 24.6 us with one row in flight,
-// 21.5 with four, 17.0 with both (6.4 TB/s read and written); 500K of 120
-// bytes 96, 66 and 52; 2M of 400 bytes 305, 296 and 276.
+// NT (an output larger than the last-level cache, pull_streams) writes past
+// the caches.  Measured on new keys each call, with one row in flight and with
+// four: 213K rows of 256 bytes 22.2 and 19.9 us, 270K of 200 bytes 72 and 40,
+// 500K of 400 bytes 98 and 76; 1.17M of 256 bytes 121 with one, 99 with four,
+// 90 with four and NT (6.7 TB/s read and written).
 template <int NE>
 constexpr int PULL_ROWS = NE <= 4 ? 4 : 1;
 

@@ -1,0 +1,14 @@
+// Prints the launch rules' decisions at the sizes given on the command line.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "rules.hpp"
+
+int main(int argc, char** argv) {
+  if (argc == 4 && !std::strcmp(argv[1], "pull_streams"))
+    std::printf("%d\n", adapm::pull_streams(std::atoll(argv[2]), std::atoll(argv[3])));
+  else
+    return 1;
+  return 0;
+}

@@ -14,10 +14,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
 @pytest.mark.parametrize("dim", [4, 13, 64, 100, 256, 300, 512])
-@pytest.mark.parametrize("n", [1, 5, 63, 1027, "large"])
+@pytest.mark.parametrize("n", [1, 5, 63, 1027, "large", "streamed"])
 def test_pull_sizes(n, dim, bf16):
     if n == "large":
         n = (32 << 20) // (4 * dim) + 3
+    elif n == "streamed":
+        n = (256 << 20) // (4 * dim) + 3
     say(f"pull n {n} dim {dim} bf16 {bf16}")
     K = 5000
     rng = np.random.default_rng(dim)

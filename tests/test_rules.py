@@ -1,0 +1,26 @@
+"""The size rules of the launches, from a host build of their header.  (CPU only.)"""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2206_00470_amd", "csrc")
+LLC = 256 << 20   # bytes of the last-level cache
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("rules") / "check")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-I", CSRC, "-o", exe, os.path.join(HERE, "rules_check.cpp")])
+    return lambda *a: int(subprocess.check_output([exe, *map(str, a)], text=True))
+
+
+@pytest.mark.parametrize("dim", [4, 50, 64, 100, 512, 1000])
+def test_a_pulled_output_is_streamed_only_past_the_last_level_cache(rule, dim):
+    """A reader finds a smaller output in the cache."""
+    line = LLC // (4 * dim)
+    assert rule("pull_streams", line, dim) == 0
+    assert rule("pull_streams", line + 1, dim) == 1
+    assert rule("pull_streams", (32 << 20) // (4 * dim) + 1, dim) == 0
+    assert rule("pull_streams", 2**31 - 2**20, dim) == 1
