@@ -1322,7 +1322,9 @@ ps_status ps_pull(ps_store* s, const int64_t* keys, int64_t n, float* out, void*
     RowShape shape;
     row_shape(dim, aligned16(out) && s->dim % 4 == 0, &shape);
     ps_status r = with_shape(shape, [&]<int L, int NV, int VW>() -> ps_status {
-      int64_t grid = ceil_div(n, int64_t(PULL_ROWS<NV * VW>) * (BLOCK / L));
+      constexpr int GPB = BLOCK / L;
+      const int rows = pull_rows(n, GPB, NV * VW);
+      int64_t grid = ceil_div(n, int64_t(rows) * GPB);
       if (grid > 65536) grid = 65536;
       Timed t(s, PS_KERNEL_PULL, st);
       auto launch = [&](auto kernel, auto values) {
@@ -1330,15 +1332,18 @@ ps_status ps_pull(ps_store* s, const int64_t* keys, int64_t n, float* out, void*
                            out + col0, (int64_t)s->dim, s->status, s->stg ? s->stg->map : nullptr,
                            s->stg ? s->stg->num_keys : int64_t(0));
       };
-      if (s->bf16) {
-        const bf16_t* values = reinterpret_cast<const bf16_t*>(s->W);
-        if (nt) launch(k_pull<L, NV, VW, bf16_t, true>, values);
-        else launch(k_pull<L, NV, VW, bf16_t, false>, values);
-      } else {
-        const float* values = s->W;
-        if (nt) launch(k_pull<L, NV, VW, float, true>, values);
-        else launch(k_pull<L, NV, VW, float, false>, values);
-      }
+      auto launch_rows = [&]<int U, class VT>(const VT* values) {
+        if (nt) launch(k_pull<L, NV, VW, VT, U, true>, values);
+        else launch(k_pull<L, NV, VW, VT, U, false>, values);
+      };
+      auto launch_values = [&]<class VT>(const VT* values) {
+        if constexpr (NV * VW <= 4) {
+          if (rows == 4) return launch_rows.template operator()<4>(values);
+        }
+        launch_rows.template operator()<1>(values);
+      };
+      if (s->bf16) launch_values(reinterpret_cast<const bf16_t*>(s->W));
+      else launch_values(static_cast<const float*>(s->W));
       LAUNCHED(k_pull);
       return PS_OK;
     });

@@ -24,23 +24,19 @@ struct RowShape {
 // the pulled rows are fp32 either way.
 // Pulled row i goes to out + i * out_ld (out_ld = dim, or the full row
 // width when a wide row is pulled in column slices).
-// Bound by the row reads and writes.  A group keeps PULL_ROWS rows in flight,
-// since one load per lane left it waiting for key, row and store in turn, and
-// NT (an output larger than the last-level cache, pull_streams) writes past
-// the caches.  Measured on new keys each call, with one row in flight and with
-// four: 213K rows of 256 bytes 22.2 and 19.9 us, 270K of 200 bytes 72 and 40,
+// Bound by the row reads and writes.  A group keeps U rows in flight
+// (pull_rows): one load per lane leaves it waiting for key, row and store in
+// turn.  NT (an output larger than the last-level cache, pull_streams) writes
+// past the caches.  Measured on new keys each call, with one row in flight and
+// with four: 213K rows of 256 bytes 22.2 and 19.9 us, 270K of 200 bytes 72 and 40,
 // 500K of 400 bytes 98 and 76; 1.17M of 256 bytes 121 with one, 99 with four,
 // 90 with four and NT (6.7 TB/s read and written).
-template <int NE>
-constexpr int PULL_ROWS = NE <= 4 ? 4 : 1;
-
-template <int L, int NV, int VW, class VT, bool NT>
+template <int L, int NV, int VW, class VT, int U, bool NT>
 __global__ __launch_bounds__(BLOCK) void k_pull(const VT* __restrict__ W, int64_t ld, int64_t num_keys, int dim,
                                                 const int64_t* __restrict__ keys, int64_t n,
                                                 float* __restrict__ out, int64_t out_ld, int32_t* __restrict__ err,
                                                 const int32_t* __restrict__ map, int64_t map_keys) {
   constexpr int GPB = BLOCK / L;
-  constexpr int U = PULL_ROWS<NV * VW>;
   const int gl = threadIdx.x % L;
   int bad = 0, miss = 0;
   const int64_t S = (int64_t)gridDim.x * GPB;

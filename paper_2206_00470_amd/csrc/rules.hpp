@@ -19,4 +19,19 @@ constexpr int64_t LLC_BYTES = int64_t(256) << 20;
 // and 90.6), 500 MB 291.6 and 284.9 (alone 160 and 147).
 inline bool pull_streams(int64_t n, int64_t dim) { return n * dim * 4 > LLC_BYTES; }
 
+// Rows of a pull that one row group keeps in flight: four where a lane holds at
+// most four floats of a row and there are more workgroups than run at once
+// (eight on each of 256 compute units), else one.  Below that line four rows
+// per group only leave units empty.  Measured on the device (graph replays) in
+// rows of 64 floats, with one and with four: 8,000 rows (500 workgroups of one
+// row per group) 3.7 and 4.6 us, 32,000 (2,000) 5.6 and 6.2, 33,600 (2,100) 6.7
+// and 6.5, 96,000 (6,000) 14.5 and 12.4; the line is at the same number of
+// workgroups for rows of 4 to 256 floats.
+constexpr int64_t PULL_BLOCKS_AT_ONCE = 2048;
+
+inline int pull_rows(int64_t n, int groups_per_block, int floats_per_lane) {
+  const int64_t blocks = (n + groups_per_block - 1) / groups_per_block;
+  return floats_per_lane <= 4 && blocks > PULL_BLOCKS_AT_ONCE ? 4 : 1;
+}
+
 }  // namespace adapm

@@ -1,5 +1,5 @@
 """Pulls at the edges of their launch: rows of every lane layout, counts that
-leave groups with one to four rows, outputs below and above the size that is
+give groups one, three and four rows, outputs below and above the size that is
 written past the caches, and outputs that are not 16-byte aligned."""
 import numpy as np
 import pytest
@@ -14,9 +14,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
 @pytest.mark.parametrize("dim", [4, 13, 64, 100, 256, 300, 512])
-@pytest.mark.parametrize("n", [1, 5, 63, 1027, "large", "streamed"])
+@pytest.mark.parametrize("n", [1, 5, 63, 1027, "one row", "four rows", "large", "streamed"])
 def test_pull_sizes(n, dim, bf16):
-    if n == "large":
+    lanes = 64 if dim % 4 else next(x for x in (4, 8, 16, 32, 64) if 4 * x >= dim or x == 64)
+    if n in ("one row", "four rows"):   # the last count with one row per group, the first ones with three and four
+        n = 2048 * (256 // lanes) + (0 if n == "one row" else 5)
+    elif n == "large":
         n = (32 << 20) // (4 * dim) + 3
     elif n == "streamed":
         n = (256 << 20) // (4 * dim) + 3

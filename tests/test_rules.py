@@ -24,3 +24,15 @@ def test_a_pulled_output_is_streamed_only_past_the_last_level_cache(rule, dim):
     assert rule("pull_streams", line + 1, dim) == 1
     assert rule("pull_streams", (32 << 20) // (4 * dim) + 1, dim) == 0
     assert rule("pull_streams", 2**31 - 2**20, dim) == 1
+
+
+@pytest.mark.parametrize("groups_per_block", [64, 16, 4])
+def test_small_pulls_keep_one_row_per_group(rule, groups_per_block):
+    """Four rows per group where the groups would not all run at once anyway."""
+    line = 2048 * groups_per_block
+    for n in (1, 1000, line):
+        assert rule("pull_rows", n, groups_per_block, 4) == 1
+    for n in (line + 1, 2**31 - 2**20):
+        assert rule("pull_rows", n, groups_per_block, 4) == 4
+        assert rule("pull_rows", n, groups_per_block, 1) == 4
+        assert rule("pull_rows", n, groups_per_block, 8) == 1   # eight floats per lane are enough in flight
