@@ -273,6 +273,7 @@ struct SortBufs {
   double* fold;           // [n/(FOLD_SB*CHUNK)+1][dim]
   int64_t tiles;
   int items;              // keys per thread of a radix tile (tile = BLOCK * items keys)
+  int64_t tiled_keys = MID_KEYS_MAX;   // most keys whose work is done by the k_mid_* kernels
 };
 
 // Keys per thread of the radix tiles: small sorts get more, smaller tiles
@@ -456,13 +457,14 @@ ps_status run_segments(const SortBufs& b, const uint32_t* ks, int64_t n, int64_t
 }
 
 // The key work of a call: sort and segments, by one workgroup where the keys
-// fit it (k_small_keys), else by the kernels above.  seg_off, uniq64 and
-// split_key as for run_segments, the rest as for run_sort.
+// fit it (k_small_keys), in tiles up to b.tiled_keys (k_mid_*), else by the
+// kernels above.  seg_off, uniq64 and split_key as for run_segments, the rest
+// as for run_sort.
 template <class KS>
 ps_status run_keywork(ps_store* s, KS ks, int64_t n, int64_t num_keys, SortBufs& b, int32_t* err, uint32_t* perm_out,
                       bool want_rank, hipStream_t st, uint32_t** keys_sorted, uint32_t** perm, bool header_cleared,
                       int32_t* seg_off, int64_t* uniq64, uint32_t split_key = 0) {
-  if (n > MID_KEYS_MAX) {
+  if (n > SMALL_KEYS_MAX && n > std::min(b.tiled_keys, MID_KEYS_MAX)) {
     if (ps_status r = run_sort(s, ks, n, num_keys, b, err, perm_out, want_rank, st, keys_sorted, perm, header_cleared))
       return r;
     return run_segments(b, *keys_sorted, n, num_keys, seg_off, uniq64, st, split_key);
@@ -1413,6 +1415,8 @@ ps_status ps_push_prepare(ps_store* s, const int64_t* keys, int64_t n, void* ws,
   Plan p;
   plan_op(ws, s->num_keys, s->dim, PS_OP_PUSH, n, 1, &p);
   if (ps_status st = check_ws(p, ws, ws_bytes)) return st;
+  RowShape shape;
+  if (row_shape(std::min(s->dim, ROW_MAX), true, &shape)) p.sb.tiled_keys = push_prepare_tiled_keys(s->dim, shape.L);
   return push_prepare(s, keys, n, p, as_stream(stream));
 }
 

@@ -34,4 +34,24 @@ inline int pull_rows(int64_t n, int groups_per_block, int floats_per_lane) {
   return floats_per_lane <= 4 && blocks > PULL_BLOCKS_AT_ONCE ? 4 : 1;
 }
 
+// The most keys whose work ps_push_prepare does in tiles (sort.hpp, "middling
+// inputs", which end at MID_KEYS_MAX in any case).  A prepare runs beside another
+// push's merge, and the tiles' workgroups of 1,024 threads wait until a compute
+// unit has that many free, which a merge with more workgroups than run at once
+// leaves late; the kernels of 256 threads slip in.  So tiles are taken beside
+// short merges: 10M floats where row groups are at most 32 lanes, 28,000 keys
+// where a row of up to 256 floats takes a whole wavefront.  Wider rows' merges
+// are so long that neither shows.  Measured as graph replays of pipelined pushes
+// with kernels of 256 threads and with tiles: rows of 64 floats, 120,000 keys
+// 87 and 81 us, 200,000 96 and 98, 300,000 110 and 118; of 128, 64,000 keys 105
+// and 101, 200,000 119 and 130; of 200, 24,000 keys 80 and 74, 64,000 100 and
+// 110, 200,000 162 and 180; of 384, 60,000 keys 149 and 139.  (The prepares of
+// the steps run beside more than a merge and gain from tiles at every size:
+// factorization at rank 64 of 108,000 keys 111 and 103, 380,000 174 and 170; CTR
+// of 212,992 keys 105.0 and 104.5, 312,000 134 and 128.)
+inline int64_t push_prepare_tiled_keys(int64_t dim, int row_lanes) {
+  if (row_lanes < 64) return 10'000'000 / dim;
+  return dim <= 256 ? 28'000 : INT64_MAX;
+}
+
 }  // namespace adapm

@@ -23,7 +23,9 @@ def dev(a):
 
 
 CASES = [(1, 4, 1, None), (5000, 16, 4097, 1.1), (23_000, 100, 300_001, 1.1), (3000, 3, 2000, None),
-         (40, 64, 70_001, 1.5), (700, 512, 999, None)]
+         (40, 64, 70_001, 1.5), (700, 512, 999, None),
+         # the last key work in tiles and the first in separate kernels, by the lanes of a row
+         (9000, 128, 78_125, 1.1), (9000, 128, 78_126, 1.1), (9000, 132, 28_000, 1.1), (9000, 132, 28_001, 1.1)]
 
 
 @pytest.mark.parametrize("K,d,n,zipf", CASES)

@@ -36,3 +36,14 @@ def test_small_pulls_keep_one_row_per_group(rule, groups_per_block):
         assert rule("pull_rows", n, groups_per_block, 4) == 4
         assert rule("pull_rows", n, groups_per_block, 1) == 4
         assert rule("pull_rows", n, groups_per_block, 8) == 1   # eight floats per lane are enough in flight
+
+
+@pytest.mark.parametrize("dim,lanes,tiled,separate", [(64, 16, 120_000, 200_000), (128, 32, 64_000, 200_000),
+                                                      (200, 64, 24_000, 64_000), (140, 64, 20_000, 47_000),
+                                                      (50, 64, 28_000, 125_000)])
+def test_a_prepare_beside_a_long_merge_takes_no_tiles(rule, dim, lanes, tiled, separate):
+    assert tiled <= rule("push_prepare_tiled_keys", dim, lanes) < separate
+
+
+def test_a_prepare_beside_the_merge_of_wide_rows_takes_tiles(rule):
+    assert rule("push_prepare_tiled_keys", 300, 64) > 96 * 4096
