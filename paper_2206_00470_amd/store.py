@@ -262,6 +262,10 @@ class Store:
     def step_mf_apply(self, B: int, lam: float, ws: torch.Tensor, loss=None, stream=None, rows_done=None):
         """rows_done: a torch.cuda.Event recorded once the row-key merge is enqueued."""
         loss = self._loss(loss)
+        if rows_done is not None and not rows_done.cuda_event:
+            # a torch event has no handle before its first record; without one the
+            # library would record nothing and a wait for the event would not wait
+            rows_done.record(*(() if stream is None else (stream,)))
         ev = C.c_void_p(rows_done.cuda_event) if rows_done is not None else C.c_void_p(0)
         check(lib().ps_step_mf_apply(self._h, B, lam, _ptr(loss), _ptr(ws), ws.numel(), _stream(stream), ev))
         return loss
