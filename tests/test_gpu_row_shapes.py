@@ -9,13 +9,14 @@ import torch
 
 import oracle
 from paper_2206_00470_amd import Store
-from paper_2206_00470_amd.workloads import (CTR_33M, MF_10Mx1M, SGNS_1M, CTRWorkload, MFWorkload, SGNSWorkload,
-                                            small_variant)
+from paper_2206_00470_amd.workloads import (CTR_33M, KGE_COMPLEX, MF_10Mx1M, SGNS_1M, CTRWorkload, KGEWorkload,
+                                            MFWorkload, SGNSWorkload, small_variant)
 from tests.helpers import assert_close_tables, say
 
 pytestmark = pytest.mark.gpu
 
-DIMS = [4, 8, 12, 16, 20, 28, 32, 36, 64, 68, 100, 128, 132, 256, 260, 384, 512]
+DIMS = [4, 8, 12, 16, 20, 28, 32, 36, 64, 68, 100, 128, 132, 256, 260, 384, 512]   # four floats per lane
+DIMS += [1, 2, 13, 50, 63, 65, 127, 129, 255, 257, 511]                             # one float per lane
 
 
 def dev(a):
@@ -75,3 +76,18 @@ def test_steps_of_every_row_width(dim, rowwise):
     rloss = (oracle.step_rowwise("ctr", W, G, (b.keys, b.label), lr, eps) if rowwise
              else oracle.step_ctr(W, G, b.keys, b.label, lr, eps))[0]
     check("ctr", Wt, Gt, W, G, loss, rloss)
+
+    if dim % 2:
+        return                     # ComplEx rows are pairs
+    kg = replace(small_variant(KGE_COMPLEX), cdim=dim // 2, n_ent=700, n_rel=11, batch=41, n_triples=410, n_neg=14,
+                 n_head_neg=7)
+    b = KGEWorkload(kg).batch(0)
+    say("  kge")
+    W, G = tables(kg.num_keys, dim, rowwise, dim + 3)
+    Wt, Gt = dev(W), dev(G)
+    s = Store(Wt, Gt, lr, eps)
+    loss = s.step_kge(dev(b.head), dev(b.rel), dev(b.tail), dev(b.neg), kg.n_head_neg, kg.n_ent)
+    assert s.error() == 0
+    args = (b.head, b.rel, b.tail, b.neg, kg.n_head_neg, kg.n_ent)
+    rloss = (oracle.step_rowwise("kge", W, G, args, lr, eps) if rowwise else oracle.step_kge(W, G, *args, lr, eps))[0]
+    check("kge", Wt, Gt, W, G, loss, rloss)
