@@ -86,7 +86,7 @@ def parse():
 
 # device code of the sort, merge and task kernels and their launches: the
 # committed counters stay valid while these files are unchanged
-COUNTER_SOURCES = ("common.hpp", "fp64math.hpp", "push.hpp", "sort.hpp", "tasks.hpp", "api.hip")
+COUNTER_SOURCES = ("common.hpp", "fp64math.hpp", "push.hpp", "rules.hpp", "sort.hpp", "tasks.hpp", "api.hip")
 
 
 def source_hash() -> str:

@@ -367,7 +367,8 @@ const char* ps_last_error_message(void);
  * measurement should time only the kernels it reports.  ps_read_timing()
  * synchronizes those events and returns the summed duration (ms) and launch
  * count of one kernel since the last reset, then resets it.  kernel_id: 0 = segmented reduce + AdaGrad, 1 = task gradient
- * (MF: the per-entry record scatter), 2 = radix scatter, 3 = pull, 4 = MF
+ * (MF: the per-entry record scatter), 2 = radix scatter (calls of up to
+ * 8,192 keys, whose key work is one kernel: that kernel), 3 = pull, 4 = MF
  * row-key merge that also forms the MF gradients and loss (timed under 4,
  * not 0), 5 = row moves of a staged store between its home tables and its
  * slots (on the staging stream; set the mask while no round runs on the

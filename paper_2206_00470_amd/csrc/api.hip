@@ -561,26 +561,33 @@ constexpr bool src_runs_on() {
     return std::is_same_v<T, void> || std::is_same_v<T, VT>;
 }
 
+// Whether a merge of n occurrences streams its table and gradient rows past
+// the caches (non-temporal): where the rows it can touch (value and
+// accumulator rows of at most min(n, num_keys) keys) exceed the last-level
+// cache.  That is a bound the host knows; the distinct keys may be far fewer,
+// and rows that fit the cache are then streamed too.  Measured over streams of
+// new batches, cached and streamed.  Above the line: pushes of 2M keys in rows
+// of 100 floats 0.837 and 0.759 ms, factorization of 1M entries at rank 100
+// 1.047 and 0.954, ComplEx of 422K occurrences of 256 floats 0.565 and 0.528,
+// skip-gram of 5,000 centres x 20 negatives over 1M words of 100 floats 0.397
+// and 0.381; with many duplicates CTR of 32,768 samples 0.318 and 0.313, 2M
+// keys over 300,000 rows of 128 floats 0.492 and 0.451, but skip-gram of 5,000
+// centres over 100,000 words of 300 floats, which come back batch after batch,
+// 0.261 and 0.273.  Below it: CTR of 8,192 samples 0.141 and 0.148, row-wise
+// factorization of 100,003 entries at rank 50 0.148 and 0.160, skip-gram of
+// 5,003 centres over 100,000 words of 100 floats 0.161 and 0.167, but
+// factorization of 150,000 entries at rank 100 0.224 and 0.214.
+bool streams_rows(const ps_store* s, int64_t n) {
+  const int64_t value_bytes = (s->bf16 ? 2 : 4) * (int64_t)s->dim;
+  const int64_t accum_bytes = s->rowwise ? 4 : 4 * (int64_t)s->dim;
+  return std::min(n, s->num_keys) * (value_bytes + accum_bytes) > LLC_BYTES;
+}
+
 // grid_cap 0: the default cap, 1,024 workgroups for rows of at most 32
 // lanes (each row group then walks more chunks, whose metadata it fetches
 // 32 at a time; measured on pushes of 400-byte rows: 0.937 -> 0.917 ms, of
 // 256-byte rows 0.123 -> 0.112 ms), MERGE_GRID_MAX for wider rows (no gain
 // there, 1% lost on 1,200-byte rows).
-// Whether a merge of n occurrences streams its table and gradient rows past
-// the caches (non-temporal).  It does when the rows it can touch (value and
-// accumulator rows of the distinct keys, at most min(n, num_keys)) exceed the
-// 256 MB last-level cache, so none of them can still be there when they are
-// next used.  Measured: pushes of 2M 400-byte rows 0.92 -> 0.80 ms, of 400K
-// 4,000-byte rows 1.40 -> 1.12, the ComplEx step (422K rows of 1 KB) 0.59 ->
-// 0.54; below the line rows are found in the cache by the next step and the
-// hint costs: CTR (213K rows of 256 bytes) 0.151 -> 0.161, a row-wise MF step
-// of 100K entries 0.176 -> 0.186.
-bool streams_rows(const ps_store* s, int64_t n) {
-  const int64_t value_bytes = (s->bf16 ? 2 : 4) * (int64_t)s->dim;
-  const int64_t accum_bytes = s->rowwise ? 4 : 4 * (int64_t)s->dim;
-  return std::min(n, s->num_keys) * (value_bytes + accum_bytes) > (int64_t(256) << 20);
-}
-
 template <class Src>
 ps_status launch_segreduce(ps_store* s, const SortBufs& b, const uint32_t* ks, Src src, int64_t n, int part,
                            hipStream_t st, int timing_id = PS_KERNEL_SEGREDUCE, int64_t grid_cap = 0,

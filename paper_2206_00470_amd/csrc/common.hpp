@@ -343,8 +343,9 @@ __device__ __forceinline__ void val_store(bf16_t* p, float x) { p->bits = (uint1
 // ------------------------------------------------------------------ streamed rows
 // The same accesses with the non-temporal hint when NT: for rows that one
 // launch touches once, so that they leave the caches to what is read again.
+// bf16 values held one per lane (rows that are no multiple of four) are
+// accessed through the caches either way.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 template <int VW, bool NT, class VT>
@@ -355,10 +356,8 @@ __device__ __forceinline__ void load_row(const VT* p, float* out) {
     if constexpr (VW == 4) {
       const f32x4 x = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
       out[0] = x.x; out[1] = x.y; out[2] = x.z; out[3] = x.w;
-    } else if constexpr (VW == 2) {
-      const f32x2 x = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(p));
-      out[0] = x.x; out[1] = x.y;
     } else {
+      static_assert(VW == 1, "rows are held four floats or one per lane");
       out[0] = __builtin_nontemporal_load(p);
     }
   } else if constexpr (VW == 4) {
@@ -379,9 +378,8 @@ __device__ __forceinline__ void store_row(VT* p, const float* in) {
   } else if constexpr (std::is_same_v<VT, float>) {
     if constexpr (VW == 4) {
       __builtin_nontemporal_store(f32x4{in[0], in[1], in[2], in[3]}, reinterpret_cast<f32x4*>(p));
-    } else if constexpr (VW == 2) {
-      __builtin_nontemporal_store(f32x2{in[0], in[1]}, reinterpret_cast<f32x2*>(p));
     } else {
+      static_assert(VW == 1, "rows are held four floats or one per lane");
       __builtin_nontemporal_store(in[0], p);
     }
   } else if constexpr (VW == 4) {

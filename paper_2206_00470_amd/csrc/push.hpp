@@ -290,9 +290,10 @@ __device__ __forceinline__ int64_t xcd_slot(int64_t block, int64_t nblocks) {
 // G[key * gld]; otherwise G is a table of rows at G + key * gld.
 // NT: the key's table rows, and the gradient rows of sources that read each
 // once, bypass the caches (streams_rows in the launch code decides).  Bound
-// by the random read-modify-write of 8*dim-byte spans: a bare probe of that
-// pattern on 1M of 11M 800-byte rows reaches 3.6 TB/s cached and 4.1 TB/s
-// non-temporal (1 KB rows: 4.8 either way, 2 KB 4.8 and 4.9; a copy 4.8-5.6).
+// by the random read-modify-write of 8*dim-byte spans: a kernel that does only
+// that, on 1M distinct spans of a table in key order, reaches cached and
+// non-temporal 3.6 and 4.2 TB/s on spans of 800 bytes, 3.4 and 3.6 on 512
+// bytes, 4.9 and 5.1 on 1 KB, 4.9 and 5.0 on 2 KB; a copy of 4 GiB moves 5.2.
 template <int L, int NV, int VW, class Src, bool RW, class VT, bool NT>
 __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_t n, VT* __restrict__ W,
                                                      float* __restrict__ G, int64_t ld, int64_t gld, int dim,

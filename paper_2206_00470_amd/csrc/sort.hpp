@@ -629,8 +629,9 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small_keys(KS ks, int n, uint32
 // Up to MID_KEYS_MAX keys: the same steps in tiles of 4,096 keys, so few that
 // a scatter adds up the tiles' digit counts by itself and the segment pass
 // the tiles' segment counts: neither scan is a launch, and nothing needs
-// clearing first.  Eight launches for three passes instead of fourteen, each
-// of four to five microseconds at these sizes.  Measured: pushes of 16 floats
+// clearing first.  Eight launches for three passes instead of thirteen (twelve
+// where the validity kernel clears the header), each of four to five
+// microseconds at these sizes.  Measured: pushes of 16 floats
 // of 16,000 keys 75 -> 63 us, of 50,000 79 -> 71, of 200,000 92 -> 90; CTR of
 // 212,992 keys 158 -> 151, skip-gram of 305,183 177 -> 166.  The counts that
 // a scatter adds up grow with the tiles: pushes of 500,000 keys take 112 us
