@@ -1324,12 +1324,12 @@ ps_status ps_pull(ps_store* s, const int64_t* keys, int64_t n, float* out, void*
   if (n == 0) return PS_OK;
   if (!keys || !out) return fail(PS_ERR_INVALID, "keys or out is NULL");
   hipStream_t st = as_stream(stream);
-  const bool nt = pull_streams(n, s->dim);
   // rows of up to ROW_MAX floats in one pass; wider rows one column slice at a time
   for (int64_t col0 = 0; col0 < s->dim; col0 += ROW_MAX) {
     const int dim = (int)std::min<int64_t>(ROW_MAX, s->dim - col0);
     RowShape shape;
     row_shape(dim, aligned16(out) && s->dim % 4 == 0, &shape);
+    const bool nt = pull_streams(n, s->dim, shape.VW);
     ps_status r = with_shape(shape, [&]<int L, int NV, int VW>() -> ps_status {
       constexpr int GPB = BLOCK / L;
       const int rows = pull_rows(n, GPB, NV * VW);

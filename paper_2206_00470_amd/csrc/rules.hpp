@@ -17,7 +17,22 @@ constexpr int64_t LLC_BYTES = int64_t(256) << 20;
 // and 44.8 us (the pull alone 20.1 and 20.7), 128 MB 67.6 and 84.3, 80 MB in
 // rows of 512 48.0 and 56.4; above the line 300 MB 177.6 and 177.1 (alone 99.0
 // and 90.6), 500 MB 291.6 and 284.9 (alone 160 and 147).
-inline bool pull_streams(int64_t n, int64_t dim) { return n * dim * 4 > LLC_BYTES; }
+// Two kinds of rows write lines in parts, which costs more when they are
+// streamed.  Rows stored one float per lane (`floats_per_store` 1: no multiple
+// of four, or an unaligned output) and wider than a wavefront never are: 1.2 GB
+// in rows of 130 floats 564 us cached and 664 streamed, of 301 498 and 594.
+// Rows of 257 to 512 floats that share 64-byte pieces are up to 1 GiB, as it
+// costs more the larger the output is: rows of 300 floats 0.6 GB 223 and 209
+// us, 4.8 GB 1,731 and 1,906; of 500 0.6 GB 210 and 191, 4.8 GB 1,673 and 1,729;
+// but of 400 4.8 GB 1,585 and 1,464, of 512 1,540 and 1,429, and narrower or
+// wider rows at every size (100 floats 1.2 GB 455 and 419, 1,000 4.8 GB 2,040
+// and 1,856).
+inline bool pull_streams(int64_t n, int64_t dim, int floats_per_store) {
+  const int64_t bytes = n * dim * 4;
+  if (bytes <= LLC_BYTES) return false;
+  if (floats_per_store == 1 && dim > 64) return false;
+  return dim <= 256 || dim > 512 || dim % 16 == 0 || bytes <= (int64_t(1) << 30);
+}
 
 // Rows of a pull that one row group keeps in flight: four where a lane holds at
 // most four floats of a row and there are more workgroups than run at once

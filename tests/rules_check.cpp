@@ -6,8 +6,8 @@
 #include "rules.hpp"
 
 int main(int argc, char** argv) {
-  if (argc == 4 && !std::strcmp(argv[1], "pull_streams"))
-    std::printf("%d\n", adapm::pull_streams(std::atoll(argv[2]), std::atoll(argv[3])));
+  if (argc == 5 && !std::strcmp(argv[1], "pull_streams"))
+    std::printf("%d\n", adapm::pull_streams(std::atoll(argv[2]), std::atoll(argv[3]), std::atoi(argv[4])));
   else if (argc == 5 && !std::strcmp(argv[1], "pull_rows"))
     std::printf("%d\n", adapm::pull_rows(std::atoll(argv[2]), std::atoi(argv[3]), std::atoi(argv[4])));
   else if (argc == 4 && !std::strcmp(argv[1], "push_prepare_tiled_keys"))

@@ -16,14 +16,27 @@ def rule(tmp_path_factory):
     return lambda *a: int(subprocess.check_output([exe, *map(str, a)], text=True))
 
 
-@pytest.mark.parametrize("dim", [4, 50, 64, 100, 512, 1000])
-def test_a_pulled_output_is_streamed_only_past_the_last_level_cache(rule, dim):
+@pytest.mark.parametrize("dim,per_store", [(4, 4), (50, 1), (64, 4), (100, 4), (512, 4), (1000, 4)])
+def test_a_pulled_output_is_streamed_only_past_the_last_level_cache(rule, dim, per_store):
     """A reader finds a smaller output in the cache."""
     line = LLC // (4 * dim)
-    assert rule("pull_streams", line, dim) == 0
-    assert rule("pull_streams", line + 1, dim) == 1
-    assert rule("pull_streams", (32 << 20) // (4 * dim) + 1, dim) == 0
-    assert rule("pull_streams", 2**31 - 2**20, dim) == 1
+    assert rule("pull_streams", line, dim, per_store) == 0
+    assert rule("pull_streams", line + 1, dim, per_store) == 1
+    assert rule("pull_streams", (32 << 20) // (4 * dim) + 1, dim, per_store) == 0
+    assert rule("pull_streams", 2**31 - 2**20, dim, per_store) == 1
+
+
+def test_rows_that_write_lines_in_parts_are_not_streamed(rule):
+    """Rows of one float per lane wider than a wavefront never, rows of 257 to
+    512 floats that share 64-byte pieces not into a large output."""
+    for dim in (65, 130, 301, 511):
+        for gb in (0.3, 1, 5, 20):
+            assert rule("pull_streams", int(gb * 1e9) // (4 * dim), dim, 1) == 0
+    assert rule("pull_streams", 10**9 // 1024, 256, 1) == 0     # an unaligned output
+    for dim, large in ((260, 0), (300, 0), (500, 0), (272, 1), (400, 1), (512, 1), (100, 1), (252, 1), (516, 1), (1000, 1)):
+        assert rule("pull_streams", 5 * 10**8 // (4 * dim), dim, 4) == 1
+        for gb in (2, 5, 20):
+            assert rule("pull_streams", gb * 10**9 // (4 * dim), dim, 4) == large
 
 
 @pytest.mark.parametrize("groups_per_block", [64, 16, 4])
