@@ -174,6 +174,25 @@ __device__ __forceinline__ T group_pod(const T& v, int src) {
   }
 }
 
+// Waits for loaded metadata where it is called (an empty instruction that needs
+// the words).  In the branch that loads it: a wait after the branch would also
+// hold up the chunks that load none, and since vector loads are waited for in
+// order, they would wait there for their key's table row before they could ask
+// for their gradient rows.
+template <class T>
+__device__ __forceinline__ void settle_pod(T& v) {
+  if constexpr (!std::is_empty_v<T>) {
+    union U {
+      T t;
+      uint32_t w[sizeof(T) / 4];
+    } u;
+    u.t = v;
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) asm volatile("" : "+v"(u.w[i]));
+    v = u.t;
+  }
+}
+
 // Gradient rows in occurrence order, ld floats apart, read through the sort
 // permutation.
 struct SrcIndirect {
@@ -347,7 +366,10 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
     VT* wrow = W + (int64_t)key * ld;
     float* grow = G + (int64_t)key * gld;
     float wv[NE], gv[NE];
-    float gacc = 0.0f;   // RW: the key's accumulator
+    // RW: the key's accumulator, read for split chunks as well: in the branch below
+    // it made that one end in copies of the row's words, which waited for them
+    float gacc = 0.0f;
+    if constexpr (RW) gacc = *grow;
     if (whole || Src::kNeedsOwn) {   // issue the table reads early, they do not depend on the sum
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -357,7 +379,6 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
           if (!RW && whole) load_row<VW, NT>(grow + col, gv + v * VW);
         }
       }
-      if (RW && whole) gacc = *grow;
     }
     double acc[NE];
 #pragma unroll
@@ -366,7 +387,10 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
       const int cnt = j1 - jb < L ? j1 - jb : L;
       Meta mine{};
       if (jb == j0 && gl == 0) mine = first;            // prefetched with the chunk bounds
-      else if (gl < cnt) mine = src.meta(jb + gl);
+      else if (gl < cnt) {
+        mine = src.meta(jb + gl);
+        settle_pod(mine);
+      }
       int q = 0;
       for (; q + UNROLL <= cnt; q += UNROLL) {
         Elem x[UNROLL][NE];
