@@ -561,28 +561,6 @@ constexpr bool src_runs_on() {
     return std::is_same_v<T, void> || std::is_same_v<T, VT>;
 }
 
-// Whether a merge of n occurrences streams its table and gradient rows past
-// the caches (non-temporal): where the rows it can touch (value and
-// accumulator rows of at most min(n, num_keys) keys) exceed the last-level
-// cache.  That is a bound the host knows; the distinct keys may be far fewer,
-// and rows that fit the cache are then streamed too.  Measured over streams of
-// new batches, cached and streamed.  Above the line: pushes of 2M keys in rows
-// of 100 floats 0.837 and 0.759 ms, factorization of 1M entries at rank 100
-// 1.047 and 0.954, ComplEx of 422K occurrences of 256 floats 0.565 and 0.528,
-// skip-gram of 5,000 centres x 20 negatives over 1M words of 100 floats 0.397
-// and 0.381; with many duplicates CTR of 32,768 samples 0.318 and 0.313, 2M
-// keys over 300,000 rows of 128 floats 0.492 and 0.451, but skip-gram of 5,000
-// centres over 100,000 words of 300 floats, which come back batch after batch,
-// 0.261 and 0.273.  Below it: CTR of 8,192 samples 0.141 and 0.148, row-wise
-// factorization of 100,003 entries at rank 50 0.148 and 0.160, skip-gram of
-// 5,003 centres over 100,000 words of 100 floats 0.161 and 0.167, but
-// factorization of 150,000 entries at rank 100 0.224 and 0.214.
-bool streams_rows(const ps_store* s, int64_t n) {
-  const int64_t value_bytes = (s->bf16 ? 2 : 4) * (int64_t)s->dim;
-  const int64_t accum_bytes = s->rowwise ? 4 : 4 * (int64_t)s->dim;
-  return std::min(n, s->num_keys) * (value_bytes + accum_bytes) > LLC_BYTES;
-}
-
 // grid_cap 0: the default cap, 1,024 workgroups for rows of at most 32
 // lanes (each row group then walks more chunks, whose metadata it fetches
 // 32 at a time; measured on pushes of 400-byte rows: 0.937 -> 0.917 ms, of
@@ -599,17 +577,19 @@ ps_status launch_segreduce(ps_store* s, const SortBufs& b, const uint32_t* ks, S
   float* W = s->W + (s->bf16 ? 0 : cs.col0);
   bf16_t* Wb = reinterpret_cast<bf16_t*>(s->W) + (s->bf16 ? cs.col0 : 0);
   float* G = s->G + (s->rowwise ? 0 : cs.col0);
-  const bool stream_rows = streams_rows(s, n);
+  const bool stream_rows = merge_streams(std::min(n, s->num_keys), s->dim, s->rowwise, s->bf16, s->G == s->W + s->dim);
   return with_shape(shape, [&]<int L, int NV, int VW>() -> ps_status {
     const int64_t grid = reduce_grid(n, L, grid_cap ? grid_cap : (L <= 32 ? 1024 : MERGE_GRID_MAX));
     Timed t(s, timing_id, st);
+    auto launch_nt = [&]<bool RW, class VT, bool NT>(VT* values) {
+      hipLaunchKernelGGL((k_segreduce<L, NV, VW, Src, RW, VT, NT>), dim3(grid), dim3(BLOCK), 0, st, sv, src, n, values,
+                         G, s->ld, s->gld, dim, s->lr, s->eps, b.partial, b.split_list, b.hdr, part);
+    };
     auto launch = [&]<bool RW, class VT>(VT* values) {
-      if (stream_rows)
-        hipLaunchKernelGGL((k_segreduce<L, NV, VW, Src, RW, VT, true>), dim3(grid), dim3(BLOCK), 0, st, sv, src, n,
-                           values, G, s->ld, s->gld, dim, s->lr, s->eps, b.partial, b.split_list, b.hdr, part);
-      else
-        hipLaunchKernelGGL((k_segreduce<L, NV, VW, Src, RW, VT, false>), dim3(grid), dim3(BLOCK), 0, st, sv, src, n,
-                           values, G, s->ld, s->gld, dim, s->lr, s->eps, b.partial, b.split_list, b.hdr, part);
+      if constexpr (VW == 4 || RW) {   // (others are never streamed)
+        if (stream_rows) return launch_nt.template operator()<RW, VT, true>(values);
+      }
+      launch_nt.template operator()<RW, VT, false>(values);
     };
     if (s->bf16) {
       if constexpr (src_runs_on<Src, bf16_t>()) launch.template operator()<false, bf16_t>(Wb);

@@ -343,8 +343,6 @@ __device__ __forceinline__ void val_store(bf16_t* p, float x) { p->bits = (uint1
 // ------------------------------------------------------------------ streamed rows
 // The same accesses with the non-temporal hint when NT: for rows that one
 // launch touches once, so that they leave the caches to what is read again.
-// bf16 values held one per lane (rows that are no multiple of four) are
-// accessed through the caches either way.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -360,14 +358,13 @@ __device__ __forceinline__ void load_row(const VT* p, float* out) {
       static_assert(VW == 1, "rows are held four floats or one per lane");
       out[0] = __builtin_nontemporal_load(p);
     }
-  } else if constexpr (VW == 4) {
+  } else {
+    static_assert(VW == 4, "bf16 values held one per lane are not streamed");
     const u32x2 x = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
     out[0] = bf16_widen(x.x & 0xffffu);
     out[1] = bf16_widen(x.x >> 16);
     out[2] = bf16_widen(x.y & 0xffffu);
     out[3] = bf16_widen(x.y >> 16);
-  } else {
-    load_vals<VW>(p, out);
   }
 }
 
@@ -382,11 +379,10 @@ __device__ __forceinline__ void store_row(VT* p, const float* in) {
       static_assert(VW == 1, "rows are held four floats or one per lane");
       __builtin_nontemporal_store(in[0], p);
     }
-  } else if constexpr (VW == 4) {
+  } else {
+    static_assert(VW == 4, "bf16 values held one per lane are not streamed");
     const u32x2 x = {bf16_narrow(in[0]) | (bf16_narrow(in[1]) << 16), bf16_narrow(in[2]) | (bf16_narrow(in[3]) << 16)};
     __builtin_nontemporal_store(x, reinterpret_cast<u32x2*>(p));
-  } else {
-    store_vals<VW>(p, in);
   }
 }
 

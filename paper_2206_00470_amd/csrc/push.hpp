@@ -308,7 +308,7 @@ __device__ __forceinline__ int64_t xcd_slot(int64_t block, int64_t nblocks) {
 // RW selects row-wise AdaGrad: G then holds one accumulator per key, at
 // G[key * gld]; otherwise G is a table of rows at G + key * gld.
 // NT: the key's table rows, and the gradient rows of sources that read each
-// once, bypass the caches (streams_rows in the launch code decides).  Bound
+// once, bypass the caches (merge_streams decides).  Bound
 // by the random read-modify-write of 8*dim-byte spans: a kernel that does only
 // that, on 1M distinct spans of a table in key order, reaches cached and
 // non-temporal 3.6 and 4.2 TB/s on spans of 800 bytes, 3.4 and 3.6 on 512

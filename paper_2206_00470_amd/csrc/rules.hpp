@@ -69,4 +69,41 @@ inline int64_t push_prepare_tiled_keys(int64_t dim, int row_lanes) {
   return dim <= 256 ? 28'000 : INT64_MAX;
 }
 
+// Whether a merge streams its table and gradient rows past the caches
+// (non-temporal).  First, where the rows it can touch (value and accumulator rows
+// of at most `keys` keys, the smaller of occurrences and table rows) exceed the
+// last-level cache.  That is a bound the host knows; the distinct keys may be far
+// fewer, and rows that fit the cache are then streamed too.  Measured over streams
+// of new batches, cached and streamed.  Above the line: pushes of 2M keys in rows
+// of 100 floats 0.837 and 0.759 ms, factorization of 1M entries at rank 100
+// 1.047 and 0.954, ComplEx of 422K occurrences of 256 floats 0.565 and 0.528,
+// skip-gram of 5,000 centres x 20 negatives over 1M words of 100 floats 0.397
+// and 0.381; with many duplicates CTR of 32,768 samples 0.318 and 0.313, 2M
+// keys over 300,000 rows of 128 floats 0.492 and 0.451, but skip-gram of 5,000
+// centres over 100,000 words of 300 floats, which come back batch after batch,
+// 0.261 and 0.273.  Below it: CTR of 8,192 samples 0.141 and 0.148, row-wise
+// factorization of 100,003 entries at rank 50 0.148 and 0.160, skip-gram of
+// 5,003 centres over 100,000 words of 100 floats 0.161 and 0.167, but
+// factorization of 150,000 entries at rank 100 0.224 and 0.214.
+// Second, where rows do not leave too many cache lines in parts: streamed, two
+// keys' parts of one line go out separately.  Pushes of 4M keys, cached and
+// streamed (us): two tables of 64 floats 949 and 918, of 100 1,775 and 1,699, of
+// 200 3,022 and 2,741, but of 36 947 and 986, 50 1,157 and 1,290, 65 1,369 and
+// 1,558, 130 2,195 and 2,291; the two rows of a key side by side (`together`) of
+// 28 floats 751 and 728, 60 1,169 and 1,066, but of 20 643 and 655, 50 1,055 and
+// 1,078, 65 1,262 and 1,386; row-wise of 20 585 and 602, 50 953 and 977, 64 880
+// and 836, 130 1,538 and 1,551, 200 2,078 and 1,845, 250 2,559 and 2,288; bf16 of
+// 28 719 and 771, 60 1,053 and 1,079, 64 899 and 861, 101 1,567 and 1,635, 200
+// 2,502 and 2,299.  Rows of no multiple of four floats are stored one float per
+// lane.
+inline bool merge_streams(int64_t keys, int64_t dim, bool rowwise, bool bf16, bool together) {
+  const int64_t value_bytes = (bf16 ? 2 : 4) * dim;
+  const int64_t accum_bytes = rowwise ? 4 : 4 * dim;
+  if (keys * (value_bytes + accum_bytes) <= LLC_BYTES) return false;
+  if (dim % 4 != 0) return rowwise && dim > 128;
+  if (dim >= 100) return true;
+  if (rowwise) return dim >= 64;
+  return value_bytes % 64 == 0 || (together && !bf16 && dim >= 28);
+}
+
 }  // namespace adapm

@@ -12,6 +12,9 @@ int main(int argc, char** argv) {
     std::printf("%d\n", adapm::pull_rows(std::atoll(argv[2]), std::atoi(argv[3]), std::atoi(argv[4])));
   else if (argc == 4 && !std::strcmp(argv[1], "push_prepare_tiled_keys"))
     std::printf("%lld\n", (long long)adapm::push_prepare_tiled_keys(std::atoll(argv[2]), std::atoi(argv[3])));
+  else if (argc == 7 && !std::strcmp(argv[1], "merge_streams"))
+    std::printf("%d\n", adapm::merge_streams(std::atoll(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]) != 0,
+                                             std::atoi(argv[5]) != 0, std::atoi(argv[6]) != 0));
   else
     return 1;
   return 0;

@@ -60,3 +60,24 @@ def test_a_prepare_beside_a_long_merge_takes_no_tiles(rule, dim, lanes, tiled, s
 
 def test_a_prepare_beside_the_merge_of_wide_rows_takes_tiles(rule):
     assert rule("push_prepare_tiled_keys", 300, 64) > 96 * 4096
+
+
+@pytest.mark.parametrize("layout", ["dense", "interleaved", "rowwise", "bf16"])
+def test_merges_stream_rows_that_leave_few_lines_in_parts(rule, layout):
+    """Rows that can exceed the last-level cache are streamed at the widths that
+    gain from it, in each layout; narrow or one-float-per-lane rows are not."""
+    args = dict(dense=(0, 0, 0), interleaved=(0, 0, 1), rowwise=(1, 0, 0), bf16=(0, 1, 0))[layout]
+    row = {"rowwise": lambda d: 4 * d + 4, "bf16": lambda d: 6 * d}.get(layout, lambda d: 8 * d)
+    yes = dict(dense=[16, 32, 48, 64, 80, 96, 100, 140, 200, 256, 300, 500, 512, 1000],
+               interleaved=[16, 28, 32, 36, 48, 60, 64, 68, 96, 100, 140, 200, 300, 512, 1000],
+               rowwise=[64, 68, 80, 96, 100, 128, 200, 300, 130, 250, 301, 511], bf16=[32, 64, 96, 100, 140, 200, 300, 512])
+    no = dict(dense=[4, 20, 28, 36, 60, 68, 13, 50, 63, 65, 101, 127, 130, 250, 511],
+              interleaved=[4, 20, 24, 13, 50, 63, 65, 101, 130, 250, 511],
+              rowwise=[4, 16, 20, 28, 32, 48, 60, 13, 50, 65, 101, 127],
+              bf16=[4, 16, 20, 28, 36, 48, 60, 68, 50, 65, 101, 130, 301])
+    for d in yes[layout]:
+        line = LLC // row(d)
+        assert rule("merge_streams", line, d, *args) == 0, d
+        assert rule("merge_streams", line + 1, d, *args) == 1, d
+    for d in no[layout]:
+        assert rule("merge_streams", 2**31 - 2**20, d, *args) == 0, d
