@@ -244,36 +244,29 @@ constexpr bool src_has_loss() {
   else return false;
 }
 
-// Sources with kCoef = true give the gradient row as coefficient x row:
-// load returns the row (elements of type Src::Elem, float otherwise) and
-// m.coef scales it on its way into the sum, each product rounded as a stored
-// fp32 gradient row would be.  Conversions, not the gathers, bounded the merge
-// of skip-gram's coefficients x fp32 rows: 17M occurrences of 300 floats took
-// 5.2 ms with the products rounded through fp32 words and two rows in flight,
-// and take 3.1 ms with round_to_24_bits and four (6.6 TB/s of rows read, most
-// of them from the caches).  Its coefficients are at most 1 in magnitude (a
-// logistic function), so the products stay in the fp32 range.  A product with
-// an fp64 row (ComplEx: a product of two fp32 rows) may leave that range and is
-// then infinite, as a stored row is: those are converted, which costs nothing
-// measurable there (a step of 422K occurrences of 256 floats 524 us either way).
+// Sources with kCoef = true give the gradient row as coefficient x fp32 row:
+// load returns the row and m.coef scales it on its way into the sum, each
+// product rounded as a stored fp32 gradient row would be.  Conversions, not the
+// gathers, bounded the merge of skip-gram's products: 17M occurrences of 300
+// floats took 5.2 ms with the products rounded through fp32 words and two rows
+// in flight, and take 3.1 ms with round_to_24_bits and four (6.6 TB/s of rows
+// read, most of them from the caches).  The coefficients are at most 1 in
+// magnitude (a logistic function), so the products stay in the fp32 range.
 template <class Src>
 constexpr bool src_has_coef() {
   if constexpr (requires { Src::kCoef; }) return Src::kCoef;
   else return false;
 }
-template <class Src> struct SrcElem { using type = float; };
-template <class Src> requires(src_has_coef<Src>()) struct SrcElem<Src> { using type = typename Src::Elem; };
 
-template <class Src, class T>
-__device__ __forceinline__ void add_element(double& acc, const typename Src::Meta& m, T x) {
-  if constexpr (!src_has_coef<Src>()) acc += (double)x;
-  else if constexpr (std::is_same_v<T, float>) acc += round_to_24_bits(m.coef * (double)x);
-  else acc += (double)(float)(m.coef * x);
+template <class Src>
+__device__ __forceinline__ void add_element(double& acc, const typename Src::Meta& m, float x) {
+  if constexpr (src_has_coef<Src>()) acc += round_to_24_bits(m.coef * (double)x);
+  else acc += (double)x;
 }
 
 template <int L, int NV, int VW, bool NT, class Src>
 __device__ __forceinline__ void src_load(const Src& src, const typename Src::Meta& m, int32_t j, const float* own,
-                                         int gl, typename SrcElem<Src>::type* x, double& lsum) {
+                                         int gl, float* x, double& lsum) {
   if constexpr (src_has_loss<Src>()) src.template load<L, NV, VW, NT>(m, j, own, gl, x, lsum);
   else src.template load<L, NV, VW, NT>(m, j, own, gl, x);
 }
@@ -323,11 +316,8 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
   constexpr int GPB = BLOCK / L;
   constexpr int NE = NV * VW;
   using Meta = typename Src::Meta;
-  using Elem = typename SrcElem<Src>::type;
   // rows in flight
-  constexpr int ROW_WORDS = NE * (int)(sizeof(Elem) / 4);
-  constexpr int UNROLL = src_has_loss<Src>() ? 1
-                       : src_has_coef<Src>() ? (sizeof(Elem) == 4 ? 4 : 2) : (ROW_WORDS <= 4 ? 4 : 2);
+  constexpr int UNROLL = src_has_loss<Src>() ? 1 : (src_has_coef<Src>() || NE <= 4 ? 4 : 2);
   const int gl = threadIdx.x % L;
   // part 0: every chunk; 1: chunks whose key reaches the split key; 2: the others
   int64_t cbeg = 0, cend = sv.hdr->num_chunks;
@@ -393,7 +383,7 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
       }
       int q = 0;
       for (; q + UNROLL <= cnt; q += UNROLL) {
-        Elem x[UNROLL][NE];
+        float x[UNROLL][NE];
         Meta m[UNROLL];
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
@@ -406,7 +396,7 @@ __global__ __launch_bounds__(BLOCK) void k_segreduce(SegView sv, Src src, int64_
           for (int e = 0; e < NE; ++e) add_element<Src>(acc[e], m[u], x[u][e]);
       }
       for (; q < cnt; ++q) {
-        Elem x[NE];
+        float x[NE];
         const Meta m = group_pod<L>(mine, q);
         src_load<L, NV, VW, NT>(src, m, jb + q, wv, gl, x, lsum);
 #pragma unroll

@@ -535,11 +535,14 @@ __global__ __launch_bounds__(BLOCK) void k_kge_grad(const float* __restrict__ W,
   if (threadIdx.x == 0) loss_part[blockIdx.x] = lsum;
 }
 
-// Gradient source of the KGE push.
+// Gradient source of the KGE push.  The products with an fp64 row are rounded
+// where the row is loaded: a product beyond the fp32 range (a row is a product
+// of two fp32 rows) is infinite, as a stored row is, and fp64 rows held until
+// the sum took longer at most widths (2,000 triples x 150 over 300,000 entities,
+// the merge: rows of 64 floats 65 and 55 us, of 128 119 and 112, of 300 236 and
+// 213, of 512 393 and 379, of 256 189 and 193).
 struct SrcKGE {
   static constexpr bool kNeedsOwn = false;
-  static constexpr bool kCoef = true;
-  using Elem = double;
   const uint32_t* perm;
   const float* mat;
   const double* base;
@@ -548,7 +551,7 @@ struct SrcKGE {
   // the fp32 stored row (s, r, o), or with kBase the fp64 base row (negatives)
   static constexpr uint32_t kBase = 1u << 31;
   struct Meta {
-    double coef;        // of a negative; 1 for a stored row
+    double coef;        // of a negative
     uint32_t row;       // row of mat, or kBase + row of base (3 per triple, below 2^31)
     uint32_t pad;
   };
@@ -560,18 +563,13 @@ struct SrcKGE {
     return {coef[occ], kBase + t * 2 + ((int)q - 3 < n_head ? 0u : 1u), 0u};
   }
   template <int L, int NV, int VW, bool NT>
-  __device__ __forceinline__ void load(const Meta& m, int32_t, const float*, int gl, double* x) const {
+  __device__ __forceinline__ void load(const Meta& m, int32_t, const float*, int gl, float* x) const {
     if (!(m.row & kBase)) {
       const float* row = mat + (int64_t)m.row * dim;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const int c = (gl + v * L) * VW;
-        if (c < dim) {
-          float t[VW];
-          load_frag<VW>(row + c, t);
-#pragma unroll
-          for (int e = 0; e < VW; ++e) x[v * VW + e] = t[e];
-        }
+        if (c < dim) load_frag<VW>(row + c, x + v * VW);
       }
     } else {
       const double* row = base + (int64_t)(m.row - kBase) * dim;
@@ -580,7 +578,7 @@ struct SrcKGE {
         const int c = (gl + v * L) * VW;
         if (c < dim)
 #pragma unroll
-          for (int e = 0; e < VW; ++e) x[v * VW + e] = row[c + e];
+          for (int e = 0; e < VW; ++e) x[v * VW + e] = (float)(m.coef * row[c + e]);
       }
     }
   }
@@ -817,7 +815,6 @@ __global__ __launch_bounds__(BLOCK) void k_sgns_grad(const float* __restrict__ W
 struct SrcSGNS {
   static constexpr bool kNeedsOwn = false;
   static constexpr bool kCoef = true;
-  using Elem = float;
   const uint32_t* perm;
   const float* mat;
   const double* coef;
