@@ -1576,6 +1576,7 @@ static ps_status step_kge_impl(ps_store* s, const int32_t* head, const int32_t* 
   plan_op(ws, s->num_keys, s->dim, PS_OP_STEP_KGE, B, 3 + n_neg, &p);
   if (ps_status r = check_ws(p, ws, ws_bytes)) return r;
   if (ps_status r = kge_valid(s, head, rel, tail, neg, B, n_neg, rel_key_offset, p, st)) return r;
+  p.sb.tiled_keys = kge_tiled_keys(s->dim, B);
   // the key sort and segments (workspace only) run on the second stream
   // beside the gradient kernel (table reads, per-unit rows)
   if (ps_status r = fork_aux(s, st)) return r;

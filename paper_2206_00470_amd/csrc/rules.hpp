@@ -69,6 +69,18 @@ inline int64_t push_prepare_tiled_keys(int64_t dim, int row_lanes) {
   return dim <= 256 ? 28'000 : INT64_MAX;
 }
 
+// The most keys whose work a ComplEx step does in tiles beside its own gradient
+// kernel, whose waves hold half of a compute unit's registers and more: where they
+// are on every unit, workgroups of 1,024 threads wait for the kernel's end.
+// Measured, kernels of 256 threads and tiles: 300 x 150 in rows of 64 floats 125
+// and 108 us, 1,300 x 150 153 and 149, 2,000 x 150 177 and 192, 12,000 x 20 196
+// and 201, 28,000 x 4 (196,000 keys) 164 without and 173 with; rows of 256 floats
+// 1,000 x 150 227 and 224, 2,400 x 150 388 and 389; of
+// 512 floats 300 x 150 251 and 250, 1,000 x 150 376 and 424.  (Skip-gram's and
+// CTR's gradient kernels leave room: skip-gram of 377,400 keys 175 and 166, CTR of
+// 390,000 184 and 182.)
+inline int64_t kge_tiled_keys(int64_t dim, int64_t triples) { return dim <= 256 && triples <= 2000 ? 200'000 : 100'000; }
+
 // Whether a merge streams its table and gradient rows past the caches
 // (non-temporal).  First, where the rows it can touch (value and accumulator rows
 // of at most `keys` keys, the smaller of occurrences and table rows) exceed the

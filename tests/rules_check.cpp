@@ -15,6 +15,8 @@ int main(int argc, char** argv) {
   else if (argc == 7 && !std::strcmp(argv[1], "merge_streams"))
     std::printf("%d\n", adapm::merge_streams(std::atoll(argv[2]), std::atoll(argv[3]), std::atoi(argv[4]) != 0,
                                              std::atoi(argv[5]) != 0, std::atoi(argv[6]) != 0));
+  else if (argc == 4 && !std::strcmp(argv[1], "kge_tiled_keys"))
+    std::printf("%lld\n", (long long)adapm::kge_tiled_keys(std::atoll(argv[2]), std::atoll(argv[3])));
   else
     return 1;
   return 0;

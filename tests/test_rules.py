@@ -81,3 +81,9 @@ def test_merges_stream_rows_that_leave_few_lines_in_parts(rule, layout):
         assert rule("merge_streams", line + 1, d, *args) == 1, d
     for d in no[layout]:
         assert rule("merge_streams", 2**31 - 2**20, d, *args) == 0, d
+
+
+@pytest.mark.parametrize("dim,triples,tiled,separate", [(64, 1300, 198_900, 276_000), (256, 1000, 153_000, 367_200),
+                                                        (512, 1000, 45_900, 153_000), (64, 28_000, 92_000, 196_000)])
+def test_key_work_beside_the_complex_gradient_takes_few_tiles(rule, dim, triples, tiled, separate):
+    assert tiled <= rule("kge_tiled_keys", dim, triples) < separate
