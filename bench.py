@@ -970,7 +970,8 @@ def measure_ops(args, wb, store, dev, rowwise, unmerged):
     tab = 2.0 * RV + 8.0 if rowwise else 2.0 * RV + 2.0 * R
     push_alg = 8.0 * n + n * R + tab * U
     pull_alg = 8.0 * n + U * RV + n * R
-    oc = counter_summary(args.workload + "_ops") if not (rowwise or unmerged or wb.values == "bf16") else None
+    oc = (counter_summary(args.workload + "_ops")
+          if not (rowwise or unmerged or wb.values == "bf16" or args.rank) else None)   # taken at the workload's own rank
     push_traffic = int(oc["push_hbm_bytes"]) if oc and "push_hbm_bytes" in oc else None
     ops = {
         "push": {"ms": round(tp * 1e3, 4), "rows_per_s": n / tp, "alg_GBps": round(push_alg / tp / 1e9, 1),
